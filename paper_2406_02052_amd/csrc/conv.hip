@@ -3968,6 +3968,7 @@ int conv_row_tiles(int dtype, const ConvArgs& a, int ep) {
   if (c32.th != 0) return c32.grid;
   const HaloShape hs = halo_shape(dtype, a);
   if (hs.tw != 0) return ((a.w + hs.tw - 1) / hs.tw) * ((a.h + hs.th - 1) / hs.th) * a.n;
+  if (const int ft = conv_flat_tiles(dtype, a, ep)) return ft;
   int bm = CONV_BM;
   if (use_staged(dtype, a)) bm = a.c_out <= 32 ? 256 : 128;
   return (a.m + bm - 1) / bm;
@@ -3977,6 +3978,7 @@ bool conv_gemm(int dtype, const ConvArgs& a, int ep, hipStream_t st) {
   if (use_1x1(dtype, a, ep)) return launch_1x1(a, ep, st);
   const int h = launch_halo_any(dtype, a, ep, st);
   if (h >= 0) return h == 1;
+  if (conv_flat(dtype, a, ep, st)) return true;
   if (use_staged(dtype, a)) return launch_staged_tiles(a, ep, st);
   if (dtype == DT_BF16) return conv_gemm_t<bf16_t>(a, ep, st);
   return conv_gemm_t<float>(a, ep, st);

@@ -71,6 +71,11 @@ bool conv_gemm(int dtype, const ConvArgs& a, int ep, hipStream_t st);
 // Number of partial-sum rows (output row tiles) conv_gemm writes for these
 // arguments and epilogue.
 int conv_row_tiles(int dtype, const ConvArgs& a, int ep);
+// Convolution on flattened pixels, any image size (conv_flat.hip): conv_gemm takes
+// it where no kernel for a particular size applies.  Its number of partial-sum rows
+// (0: it does not apply), and the launch (false, with nothing launched, then).
+int conv_flat_tiles(int dtype, const ConvArgs& a, int ep);
+bool conv_flat(int dtype, const ConvArgs& a, int ep, hipStream_t st);
 // With a.out == nullptr, conv_gemm's streaming 1x1 forward (EP_STATS) writes
 // the BN partials only.  conv1x1_couple then forms the coupling output
 // a.out = a.resid +/- (scale h + shift) with h = that conv of

@@ -1,0 +1,49 @@
+"""GPU parity of the convolutions on flattened pixels, at the edges of their tiles
+and of the rules that choose between them (the bars of tests/harness.py)."""
+import pytest
+
+import synth
+from tests.harness import check, run_step_parity
+
+pytestmark = pytest.mark.gpu
+
+B, F = synth.CIFAR_STAGE, synth.BLOCK_FP32
+NECK = synth.IMAGENET_BOTTLENECK_STAGE
+
+CASES = {
+    # one padded chunk (c = 16); a single column; 65 pixels: one past a tile
+    "bf16_c16_70x1x1": B.with_(n=70, h=1, w=1, c_half=16, blocks=1),
+    "bf16_c32_2x33x1": B.with_(n=2, h=33, w=1, blocks=1),
+    "bf16_c64_1x13x5": B.with_(n=1, h=13, w=5, c_half=64, blocks=1),
+    # the 128-pixel tile: the smallest size that takes it, its last tile ragged
+    "bf16_c32_1x233x141": B.with_(n=1, h=233, w=141, blocks=1),
+    # four K waves: the widest image whose patches fit and the next one; two and
+    # four chunks per wave
+    "bf16_c128_1x3x46": B.with_(n=1, h=3, w=46, c_half=128, blocks=1),
+    "bf16_c128_1x3x47": B.with_(n=1, h=3, w=47, c_half=128, blocks=1),
+    "bf16_c256_3x7x7": B.with_(n=3, h=7, w=7, c_half=256, blocks=1),
+    "bf16_c512_2x3x5": B.with_(n=2, h=3, w=5, c_half=512, blocks=1),
+    # more than 256 tiles of 64 x 64
+    "bf16_c128_9x30x31": B.with_(n=9, h=30, w=31, c_half=128, blocks=1),
+    # wider than any patch: the im2col kernel
+    "bf16_c32_1x2x300": B.with_(n=1, h=2, w=300, blocks=1),
+    # 1x1 convs without a kernel of their own
+    "bf16_bottleneck_c64_16_3x9x11": NECK.with_(n=3, h=9, w=11, c_half=64, c_mid=16, blocks=1),
+    "bf16_bottleneck_c256_64_2x7x7": NECK.with_(n=2, h=7, w=7, c_half=256, c_mid=64, blocks=1),
+    "fp32_c16_5x5x13": F.with_(n=5, h=5, w=13, blocks=1),
+    "fp32_c32_1x13x5": F.with_(n=1, h=13, w=5, c_half=32, blocks=1),
+    "fp32_c64_2x9x21": F.with_(n=2, h=9, w=21, c_half=64, blocks=1),
+    "fp32_c128_1x4x19": F.with_(n=1, h=4, w=19, c_half=128, blocks=1),
+    "fp32_c128_1x4x20": F.with_(n=1, h=4, w=20, c_half=128, blocks=1),
+    "fp32_bottleneck_c64_16_3x9x11": NECK.with_(n=3, h=9, w=11, c_half=64, c_mid=16, blocks=1,
+                                                dtype="fp32"),
+}
+
+
+@pytest.mark.parametrize("name,mode", [(n, m) for n, wl in CASES.items()
+                                       for m in (("isoF", "isoG") if wl.dtype == "bf16" else ("full",))])
+def test_stage_step_parity_flat(name, mode):
+    wl = CASES[name]
+    print(f"case {name} {mode}: {wl}", flush=True)
+    got, want, exact = run_step_parity(wl, bn_affine="random", mode=mode)
+    print(check(wl, mode, got, want, exact), flush=True)
