@@ -2839,198 +2839,6 @@ __global__ __launch_bounds__(256) void wgrad_staged_kernel(WgradArgs a) {
       }
 }
 
-// Halo-tile weight gradient for 3x3 / stride 1 / pad 1 bf16 convolutions with
-// C_in a multiple of 32:
-//   part[split][o][(tap, c)] = sum over the split's pixels of dh[pix][o] * x[pix + tap][c]
-// A workgroup owns one output-channel tile (BO), one 32-channel input chunk
-// and a strided set of TH x TW pixel tiles.  Per pixel tile it stores dh
-// transposed ([o][pixel]) and the (TH+2)-row input patch transposed three
-// times, pre-shifted by 0, 1 and 2 columns ([c][row][col + s]), so that the
-// MFMA operands of every tap are 16-byte aligned LDS rows.  The BN-apply +
-// ReLU prologue runs once per patch element.  The next tile is fetched into
-// registers while the current one is multiplied; the 9 taps accumulate in
-// registers across all tiles of the split.
-template <int TH, int TW, int BO, bool PRO>
-__global__ __launch_bounds__(256) void wgrad_halo_kernel(WgradArgs a) {
-  using T = bf16_t;
-  constexpr int NPIX = TH * TW;
-  static_assert(NPIX % 32 == 0 && TW % 8 == 0 && 256 % (BO / 8) == 0, "tile");
-  constexpr int HTH = TH + 2, HTW = TW + 2, HPIX = HTH * HTW;
-  constexpr int HROW = HTH * TW + 8;        // bf16 per channel row of one shifted copy
-  constexpr int DROW = NPIX + 8;            // bf16 per output-channel row of dh^T
-  constexpr int OT = BO / 16;               // output-channel MFMA tiles
-  constexpr int WPO = 4 / OT;               // waves per output-channel tile
-  constexpr int NP = 18 / WPO;              // (tap, 16-channel half) pairs per wave
-  static_assert(OT * WPO == 4 && NP * WPO == 18, "waves");
-  constexpr int H_CHUNKS = (HPIX * 4 + 255) / 256;
-  constexpr int D_CHUNKS = (NPIX * (BO / 8) + 255) / 256;
-  __shared__ __attribute__((aligned(16))) T sh[3 * 32 * HROW];
-  __shared__ __attribute__((aligned(16))) T sd[BO * DROW];
-  __shared__ float pro_tab[2][32];
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int lr = lane & 15, lg = lane >> 4;
-  const int ot = wave % OT, part = wave / OT;
-  const int o0 = blockIdx.y * BO;
-  const int chunk = blockIdx.z;
-  const int c0 = chunk * 32;
-  const int tiles_x = (a.w + TW - 1) / TW, tiles_y = (a.h + TH - 1) / TH;
-  const int ntiles = tiles_x * tiles_y * a.n;
-
-  if constexpr (PRO) {
-    if (tid < 32) {
-      pro_tab[0][tid] = a.pro_scale[c0 + tid];
-      pro_tab[1][tid] = a.pro_shift[c0 + tid];
-    }
-    __syncthreads();
-  }
-
-  const bool dhb = a.dh_h != nullptr;
-  float dk[4][8];
-  dh_coeffs(a, o0 + (tid % (BO / 8)) * 8, dk);   // this thread's output-channel group is fixed
-  // Buffer resources: padding and rows past the image load zeros without
-  // branches, so the next tile's loads stay in flight during the MFMAs.
-  const long in_bytes = static_cast<long>(a.n) * a.h * a.w * a.c_in * 2;
-  const long out_bytes = static_cast<long>(a.m) * a.c_out * 2;
-  const __amdgpu_buffer_rsrc_t r_src = make_rsrc(a.src, in_bytes);
-  const __amdgpu_buffer_rsrc_t r_dh = make_rsrc(a.dh, out_bytes);
-  const __amdgpu_buffer_rsrc_t r_dhh = make_rsrc(dhb ? a.dh_h : a.dh, out_bytes);
-  Raw8<T> rh[H_CHUNKS], rd[D_CHUNKS], rdh[D_CHUNKS];
-  uint32_t hval = 0, dval = 0;
-  auto tile_origin = [&](int t, int& img, int& p0, int& q0) {
-    const int tx = t % tiles_x;
-    const int ty = (t / tiles_x) % tiles_y;
-    img = t / (tiles_x * tiles_y);
-    p0 = ty * TH;
-    q0 = tx * TW;
-  };
-  auto load_tile = [&](int t) {
-    int img, p0, q0;
-    tile_origin(t, img, p0, q0);
-    const long base = static_cast<long>(img) * a.h * a.w;
-    hval = dval = 0;
-#pragma unroll
-    for (int i = 0; i < H_CHUNKS; ++i) {
-      const int q = tid + 256 * i;
-      const int hp = q >> 2, sub = q & 3;
-      const int hy = hp / HTW, hx = hp - hy * HTW;
-      const int ih = p0 - 1 + hy, iw = q0 - 1 + hx;
-      const bool ok = hp < HPIX && ih >= 0 && ih < a.h && iw >= 0 && iw < a.w;
-      const uint32_t off =
-          ok ? static_cast<uint32_t>(((base + static_cast<long>(ih) * a.w + iw) * a.c_in + c0 + sub * 8) * 2)
-             : BUF_OOB;
-      rh[i].set(buf_load16(r_src, off));
-      hval |= ok ? 1u << i : 0u;
-    }
-#pragma unroll
-    for (int i = 0; i < D_CHUNKS; ++i) {
-      const int q = tid + 256 * i;
-      const int pix = q / (BO / 8), og = q % (BO / 8);
-      const int ph = pix / TW, pw = pix - ph * TW;
-      const int pp = p0 + ph, qq = q0 + pw;
-      const bool ok = pix < NPIX && pp < a.h && qq < a.w && o0 + og * 8 < a.c_out;
-      const uint32_t off =
-          ok ? static_cast<uint32_t>(((base + static_cast<long>(pp) * a.w + qq) * a.c_out + o0 + og * 8) * 2)
-             : BUF_OOB;
-      rd[i].set(buf_load16(r_dh, off));
-      rdh[i].set(buf_load16(r_dhh, off));
-      dval |= ok ? 1u << i : 0u;
-    }
-  };
-  // Prologues on the landed registers (padding stays zero), then the
-  // transposed LDS layout.
-  auto park_tile = [&]() {
-#pragma unroll
-    for (int i = 0; i < H_CHUNKS; ++i) {
-      const int q = tid + 256 * i;
-      const int hp = q >> 2, sub = q & 3;
-      if (hp >= HPIX) continue;
-      if constexpr (PRO) {
-        float v[8];
-        rh[i].to_f32(v);
-#pragma unroll
-        for (int j = 0; j < 8; ++j)
-          v[j] = fmaxf(fmaf(pro_tab[0][sub * 8 + j], v[j], pro_tab[1][sub * 8 + j]), 0.f);
-        rh[i].from_f32(v);
-        if (!((hval >> i) & 1u)) rh[i].zero();
-      }
-      const int hy = hp / HTW, hx = hp - hy * HTW;
-#pragma unroll
-      for (int sft = 0; sft < 3; ++sft) {
-        const int col = hx - sft;
-        if (col < 0 || col >= TW) continue;
-        T* dst = sh + sft * 32 * HROW + hy * TW + col;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) rh[i].put(j, dst + (sub * 8 + j) * HROW);
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < D_CHUNKS; ++i) {
-      const int q = tid + 256 * i;
-      const int pix = q / (BO / 8), og = q % (BO / 8);
-      if (pix >= NPIX) continue;
-      if (dhb) {
-        Raw8<T> r = rd[i];
-        float v[8], h[8];
-        r.to_f32(v);
-        rdh[i].to_f32(h);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = fmaf(dk[0][j], v[j], fmaf(dk[1][j], h[j] - dk[3][j], dk[2][j]));
-        r.from_f32(v);
-        if (!((dval >> i) & 1u)) r.zero();
-        rd[i] = r;
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) rd[i].put(j, sd + (og * 8 + j) * DROW + pix);
-    }
-  };
-
-  f32x4_t acc[NP];
-#pragma unroll
-  for (int i = 0; i < NP; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-  // Loads are unconditional (the prefetch after the last tile re-reads tile
-  // ntiles - 1) so the number of loads in flight is the same on every path.
-  int t = blockIdx.x;
-  load_tile(min(t, ntiles - 1));
-  for (; t < ntiles; t += gridDim.x) {
-    __syncthreads();            // previous tile's operands fully consumed
-    park_tile();
-    __syncthreads();
-    load_tile(min(t + static_cast<int>(gridDim.x), ntiles - 1));
-#pragma unroll
-    for (int g = 0; g < NPIX / 32; ++g) {
-      const int pix = g * 32 + lg * 8;
-      const int ph = pix / TW, pw = pix - ph * TW;
-      Frag<T> fa;
-      fa.load(sd + (ot * 16 + lr) * DROW + pix);
-#pragma unroll
-      for (int pi = 0; pi < NP; ++pi) {
-        const int pr = part + pi * WPO;          // 0..17
-        const int tap = pr >> 1, half = pr & 1;
-        const int fr = tap / 3, fs = tap - fr * 3;
-        Frag<T> fb;
-        fb.load(sh + fs * 32 * HROW + (half * 16 + lr) * HROW + (ph + fr) * TW + pw);
-        acc[pi] = mfma(fa, fb, acc[pi]);
-      }
-    }
-  }
-
-  float* outp = a.partials + static_cast<long>(blockIdx.x) * a.c_out * a.k_tot;
-#pragma unroll
-  for (int pi = 0; pi < NP; ++pi) {
-    const int pr = part + pi * WPO;
-    const int tap = pr >> 1, half = pr & 1;
-    const int k = tap * a.c_in + c0 + half * 16 + lr;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int o = o0 + ot * 16 + lg * 4 + e;
-      if (o < a.c_out) outp[static_cast<long>(o) * a.k_tot + k] = acc[pi][e];
-    }
-  }
-}
-
 // Weight gradient on transposing LDS reads (gfx950 ds_read_b64_tr_b16):
 //   part[split][o][tap*C_in + c] = sum over the split's pixels of dh[px][o] * x[px + tap][c]
 // Both MFMA operands need pixels along the reduction, but the tensors are
@@ -3261,7 +3069,7 @@ __device__ __forceinline__ void wgrad_tr_body(const WgradArgs& a, int bx, int by
   }
   // Partials in fragment order: every (wave, fragment) owns 256 consecutive
   // floats, lane l at 4 l .. 4 l + 3, so each wave writes whole cache lines;
-  // wgrad_tr_reduce maps them back to [o][k].
+  // the split reduce maps them back to [o][k].
   const long wg_base = (static_cast<long>(by) * nbz + bz) * NW + wave;
   float* outp = a.partials + static_cast<long>(bx) * a.c_out * a.k_tot;
 #pragma unroll
@@ -3300,9 +3108,10 @@ __global__ __launch_bounds__(64 * WO * WC * WT * WP) void wgrad_tr_group_kernel(
                                                        static_cast<int>(r / nby), a.splits, nbz);
 }
 
-// Fixed-order sum over the splits of the fragment-ordered partials of
-// wgrad_tr_kernel, scaled by inv_k and added to grad[o][k].  One thread per
-// lane-quad (4 consecutive partial floats = 4 output channels of one k).
+// Fixed-order sum over the splits of the fragment-ordered partials of the
+// transposed-read and flattened-pixel weight gradients, scaled by inv_k and added
+// to grad[o][k].  One thread per lane-quad (4 consecutive partial floats = 4 output
+// channels of one k).
 // Reduce of fragment-ordered partials: 16 quads per block; the 16 thread rows
 // take splits r, r + 16, ... and the row sums are combined in a fixed order.
 // blk is the block's index within its layer's partials.
@@ -3348,12 +3157,6 @@ __device__ __forceinline__ void tr_reduce_block(const float* __restrict__ part, 
     const int o = by * mp.bo + (wo * mp.of + of) * 16 + kg * 4 + e;
     grad[static_cast<long>(o) * mp.k_tot + k] += inv_k * acc[e];
   }
-}
-
-__global__ __launch_bounds__(256) void wgrad_tr_reduce_kernel(const float* __restrict__ part,
-                                                              int splits, long numel, TrMap mp,
-                                                              float inv_k, float* __restrict__ grad) {
-  tr_reduce_block(part, splits, numel, mp, inv_k, grad, blockIdx.x);
 }
 
 // Several layers' reduces in one launch: block b belongs to the last segment
@@ -3683,10 +3486,11 @@ void launch_wgrad_bk(const WgradArgs& a, hipStream_t st) {
 // Transposed-read weight gradient: configuration for these arguments (0: not
 // applicable) and the split count it uses.
 int wgrad_tr_plan(int dtype, const WgradArgs& a, int* splits) {
+  // plans 1-6: image sizes with a kernel of their own; else the flattened pixels
   if (!(dtype == DT_BF16 && a.src2 == nullptr && a.stride == 1 && a.r == a.s &&
         (a.r == 3 || a.r == 1) && a.pad == a.r / 2 && a.p == a.h && a.q == a.w &&
         a.dh_h != nullptr))
-    return 0;
+    return wgrad_flat_plan(dtype, a, splits);
   if (static_cast<long>(a.n) * a.h * a.w * a.c_in * 2 >= static_cast<long>(BUF_OOB) ||
       static_cast<long>(a.m) * a.c_out * 2 >= static_cast<long>(BUF_OOB))
     return 0;
@@ -3702,7 +3506,7 @@ int wgrad_tr_plan(int dtype, const WgradArgs& a, int* splits) {
   } else if (a.r == 1 && a.c_in == 32 && a.c_out == 128) {
     cfg = 6; th = 1; tw = 128; bo = 128; bc = 32;
   } else {
-    return 0;
+    return wgrad_flat_plan(dtype, a, splits);
   }
   const int ntiles = a.r == 1 ? (a.m + th * tw - 1) / (th * tw)
                               : ((a.w + tw - 1) / tw) * ((a.h + th - 1) / th) * a.n;
@@ -3776,7 +3580,8 @@ bool tr_map_of(int dtype, const WgradArgs& a, TrMap* out) {
     case 4: mp = tr_map<3, 8, 8, 1, 4, 4, 1, 1, 1>(a); return true;
     case 5: mp = tr_map<1, 1, 128, 1, 2, 4, 2, 1, 1>(a); return true;
     case 6: mp = tr_map<1, 1, 128, 4, 2, 1, 2, 1, 1>(a); return true;
-    default: return false;
+    case 0: return false;
+    default: return wgrad_flat_map(dtype, a, out);
   }
 }
 
@@ -3809,25 +3614,6 @@ void wgrad_tr_reduce_group(const float* base, const TrSeg* segs, int nseg, float
   }
 }
 
-bool wgrad_tr_reduce(int dtype, const WgradArgs& a, float inv_k, float* grad, hipStream_t st) {
-  int sp = 0;
-  TrMap mp{};
-  switch (wgrad_tr_plan(dtype, a, &sp)) {
-    case 1: mp = tr_map<3, 4, 32, 1, 2, 1, 2, 3, 4>(a); break;
-    case 2: mp = tr_map<3, 4, 56, 1, 2, 1, 2, 3, 1>(a); break;
-    case 3: mp = tr_map<3, 8, 16, 1, 4, 4, 1, 3, 1>(a); break;
-    case 4: mp = tr_map<3, 8, 8, 1, 4, 4, 1, 1, 1>(a); break;
-    case 5: mp = tr_map<1, 1, 128, 1, 2, 4, 2, 1, 1>(a); break;
-    case 6: mp = tr_map<1, 1, 128, 4, 2, 1, 2, 1, 1>(a); break;
-    default: return false;
-  }
-  const long numel = static_cast<long>(a.c_out) * a.k_tot;
-  const long quads = numel / 4;
-  PETRA_LAUNCH(wgrad_tr_reduce_kernel, dim3(static_cast<unsigned>((quads + 15) / 16)), dim3(256), 0,
-               st, a.partials, a.splits, numel, mp, inv_k, grad);
-  return true;
-}
-
 bool conv_wgrad_tr_group(int dtype, const WgradArgs* args, int n, hipStream_t st) {
   if (n <= 0) return true;
   int sp = 0;
@@ -3841,7 +3627,8 @@ bool conv_wgrad_tr_group(int dtype, const WgradArgs* args, int n, hipStream_t st
     case 4: launch_wgrad_tr_group<3, 8, 8, 1, 4, 4, 1, 1, 1>(args, n, st); return true;
     case 5: launch_wgrad_tr_group<1, 1, 128, 1, 2, 4, 2, 1, 1>(args, n, st); return true;
     case 6: launch_wgrad_tr_group<1, 1, 128, 4, 2, 1, 2, 1, 1>(args, n, st); return true;
-    default: return false;
+    case 0: return false;
+    default: return wgrad_flat(dtype, args, n, st);
   }
 }
 
@@ -3854,25 +3641,9 @@ bool conv_wgrad_tr(int dtype, const WgradArgs& a, hipStream_t st) {
     case 4: launch_wgrad_tr<3, 8, 8, 1, 4, 4, 1, 1, 1>(a, st); return true;
     case 5: launch_wgrad_tr<1, 1, 128, 1, 2, 4, 2, 1, 1>(a, st); return true;
     case 6: launch_wgrad_tr<1, 1, 128, 4, 2, 1, 2, 1, 1>(a, st); return true;
-    default: return false;
+    case 0: return false;
+    default: return wgrad_flat(dtype, &a, 1, st);
   }
-}
-
-// 0: no halo kernel; 1: 4x32 tiles, 32 output channels per group; 2: 8x16 tiles, 64.
-int wgrad_halo_shape(int dtype, const WgradArgs& a) {
-  if (!(dtype == DT_BF16 && a.src2 == nullptr && a.r == 3 && a.s == 3 && a.stride == 1 &&
-        a.pad == 1 && a.c_in % 32 == 0 && a.c_out % 8 == 0 && a.p == a.h && a.q == a.w))
-    return 0;
-  if (a.w == 32 && a.c_out <= 32) return 1;
-  if (a.w == 16 && a.c_out % 64 == 0) return 2;
-  return 0;
-}
-
-int wgrad_halo_tiles(int dtype, const WgradArgs& a) {
-  const int shape = wgrad_halo_shape(dtype, a);
-  if (shape == 1) return ((a.w + 31) / 32) * ((a.h + 3) / 4) * a.n;
-  if (shape == 2) return ((a.w + 15) / 16) * ((a.h + 7) / 8) * a.n;
-  return 0;
 }
 
 namespace {
@@ -3894,21 +3665,9 @@ void launch_wgrad_staged(const WgradArgs& a, hipStream_t st) {
   }
 }
 
-template <int TH, int TW, int BO>
-void launch_wgrad_halo(const WgradArgs& a, hipStream_t st) {
-  dim3 grid(a.splits, (a.c_out + BO - 1) / BO, a.c_in / 32);
-  if (a.pro_scale != nullptr)
-    PETRA_LAUNCH((wgrad_halo_kernel<TH, TW, BO, true>), grid, dim3(256), 0, st, a);
-  else
-    PETRA_LAUNCH((wgrad_halo_kernel<TH, TW, BO, false>), grid, dim3(256), 0, st, a);
-}
-
 template <typename T>
 void wgrad_t(const WgradArgs& a, hipStream_t st) {
   if constexpr (sizeof(T) == 2) {
-    const int shape = wgrad_halo_shape(DT_BF16, a);
-    if (shape == 1) { launch_wgrad_halo<4, 32, 32>(a, st); return; }
-    if (shape == 2) { launch_wgrad_halo<8, 16, 64>(a, st); return; }
     if (a.c_out <= 32)
       launch_wgrad_staged<32, 64>(a, st);
     else

@@ -112,20 +112,20 @@ struct WgGroupTable {
   WgradArgs a[MAX_WG_GROUP];
 };
 bool conv_wgrad_tr_group(int dtype, const WgradArgs* args, int n, hipStream_t st);
-// Halo-tile weight-gradient kernel selection (0 = not applicable) and the
-// number of pixel tiles it splits over.
-int wgrad_halo_shape(int dtype, const WgradArgs& a);
-int wgrad_halo_tiles(int dtype, const WgradArgs& a);
+// The same for any image size, bf16 and fp32 (wgrad_flat.hip): wgrad_tr_plan falls
+// back to it, with plan numbers of its own (>= 16).  Plan (0: not applicable) and
+// splits, the reduce's map, and one launch of n >= 1 layers of one plan.
+int wgrad_flat_plan(int dtype, const WgradArgs& a, int* splits);
+struct TrMap;
+bool wgrad_flat_map(int dtype, const WgradArgs& a, TrMap* out);
+bool wgrad_flat(int dtype, const WgradArgs* args, int n, hipStream_t st);
 void wgrad_reduce(const float* part, int splits, long numel, float inv_k, float* grad,
                   hipStream_t st);
-// Split reduce of the transposed-read kernel's fragment-ordered partials
-// (a.partials, a.splits) into grad[o][k] += inv_k * sum; false when that
-// kernel does not apply to these arguments (use wgrad_reduce then).
-bool wgrad_tr_reduce(int dtype, const WgradArgs& a, float inv_k, float* grad, hipStream_t st);
-// Deferred form: one layer's reduce as a table entry (partials at base +
-// part_off, gradient at grad_base + w_off), false when the transposed-read
-// kernel does not apply; wgrad_tr_reduce_group then reduces many layers in one
-// launch (per element the same fixed order as wgrad_tr_reduce).
+// Split reduce of the fragment-ordered partials of the transposed-read and
+// flattened-pixel kernels.  One layer's reduce as a table entry (partials at base +
+// part_off, gradient at grad_base + w_off), false when neither kernel applies (use
+// wgrad_reduce then); wgrad_tr_reduce_group reduces many layers in one launch, per
+// element in a fixed order: grad[o][k] += inv_k * sum over a.splits.
 struct TrMap {
   int wo, of, wc, cf, wt, tpw, bo, bc, nz, c_in, k_tot;
 };

@@ -146,7 +146,7 @@ Stage::Stage(const petra_stage_desc& d) : desc(d) {
   };
   // deferred weight gradients: every layer on the transposed-read kernel
   {
-    defer_wgrad = dt == DT_BF16 && blocks.size() >= 1;
+    defer_wgrad = blocks.size() >= 1;
     for (const ConvLayer& cv : convs) {
       WgradArgs w{};
       w.n = desc.n; w.h = desc.h; w.w = desc.w; w.p = desc.h; w.q = desc.w;
@@ -284,16 +284,6 @@ void Stage::wgrad_splits(const ConvLayer& cv, int* splits, int* rows_per_split) 
   int tr_splits = 0;
   if (wgrad_tr_plan(dt, w, &tr_splits) != 0) {
     *splits = tr_splits;
-    *rows_per_split = 0;
-    return;
-  }
-  const int hshape = wgrad_halo_shape(dt, w);
-  if (hshape != 0) {
-    // pixel tiles strided over `splits` workgroups per (output tile, channel chunk)
-    const int ntiles = wgrad_halo_tiles(dt, w);
-    const int bo = hshape == 1 ? 32 : 64;
-    const int per_split = ((cv.cout + bo - 1) / bo) * (cv.cin / 32);
-    *splits = std::max(1, std::min(ntiles, 512 / std::max(1, per_split)));
     *rows_per_split = 0;
     return;
   }

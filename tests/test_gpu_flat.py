@@ -1,5 +1,8 @@
-"""GPU parity of the convolutions on flattened pixels, at the edges of their tiles
-and of the rules that choose between them (the bars of tests/harness.py)."""
+"""GPU parity of the convolutions and weight gradients on flattened pixels, at the
+edges of their tiles and of the rules that choose between them (the bars of
+tests/harness.py, without the direction anchor: that one compares the oracle's bf16
+storage model with plain fp64, which over as few rows as here, 126 in the smallest
+case, are 0.978 apart by themselves in a BN beta the GPU has to 1.7e-5)."""
 import pytest
 
 import synth
@@ -30,6 +33,19 @@ CASES = {
     # 1x1 convs without a kernel of their own
     "bf16_bottleneck_c64_16_3x9x11": NECK.with_(n=3, h=9, w=11, c_half=64, c_mid=16, blocks=1),
     "bf16_bottleneck_c256_64_2x7x7": NECK.with_(n=2, h=7, w=7, c_half=256, c_mid=64, blocks=1),
+    # weight gradients: the widest image whose patch fits and the next one; the
+    # other channel blocks of the 1x1 convs
+    "bf16_c64_1x3x63": B.with_(n=1, h=3, w=63, c_half=64, blocks=1),
+    "bf16_c64_1x3x64": B.with_(n=1, h=3, w=64, c_half=64, blocks=1),
+    "bf16_c32_1x3x79": B.with_(n=1, h=3, w=79, blocks=1),
+    "bf16_c32_1x3x80": B.with_(n=1, h=3, w=80, blocks=1),
+    "bf16_bottleneck_c64_32_2x7x9": NECK.with_(n=2, h=7, w=9, c_half=64, c_mid=32, blocks=1),
+    "bf16_bottleneck_c32_16_2x7x9": NECK.with_(n=2, h=7, w=9, c_half=32, c_mid=16, blocks=2),
+    "bf16_bottleneck_c16_16_2x7x9": NECK.with_(n=2, h=7, w=9, c_half=16, c_mid=16, blocks=1),
+    "fp32_bottleneck_c32_32_2x7x9": NECK.with_(n=2, h=7, w=9, c_half=32, c_mid=32, blocks=2,
+                                               dtype="fp32"),
+    "fp32_c64_1x3x56": F.with_(n=1, h=3, w=56, c_half=64, blocks=1),
+    "fp32_c64_1x3x62": F.with_(n=1, h=3, w=62, c_half=64, blocks=1),
     "fp32_c16_5x5x13": F.with_(n=5, h=5, w=13, blocks=1),
     "fp32_c32_1x13x5": F.with_(n=1, h=13, w=5, c_half=32, blocks=1),
     "fp32_c64_2x9x21": F.with_(n=2, h=9, w=21, c_half=64, blocks=1),
@@ -45,5 +61,5 @@ CASES = {
 def test_stage_step_parity_flat(name, mode):
     wl = CASES[name]
     print(f"case {name} {mode}: {wl}", flush=True)
-    got, want, exact = run_step_parity(wl, bn_affine="random", mode=mode)
+    got, want, exact = run_step_parity(wl, bn_affine="random", mode=mode, anchor=False)
     print(check(wl, mode, got, want, exact), flush=True)
