@@ -119,20 +119,45 @@ __global__ __launch_bounds__(256) void split_bwd_partials_kernel(
   }
 }
 
+// Elementwise over (row, 8 channels); a block's 256 threads cover whole rows
+// (c / 8 divides 256), so a thread keeps its channels' constants over APPLY_ROWS
+// rows: with one row per thread the 48 constant loads cost more than the three
+// 16-byte tensor accesses (128x32x32x64: 24.2 us).
+constexpr int APPLY_ROWS = 4;
 template <typename T>
 __global__ __launch_bounds__(256) void split_bwd_apply_kernel(
     const T* d1, const T* d2, const T* h, const float* scale, const float* shift, const float* ca,
     const float* cb, const float* cc, const float* mean, int relu, T* dh, long m, int c) {
-  const int c8 = c / 8;
-  for (long i = static_cast<long>(blockIdx.x) * 256 + threadIdx.x; i < m * c8;
-       i += static_cast<long>(gridDim.x) * 256) {
-    const long row = i / c8;
-    const int ch = static_cast<int>(i - row * c8) * 8;
-    float dz[8], hv[8], o[8];
-    load_dz(d1, d2, h, scale, shift, relu, row, ch, c, dz, hv);
+  const int c8 = c / 8, half = c / 2;
+  const int rows = 256 / c8, ch = (threadIdx.x % c8) * 8;
+  const T* src = ch < half ? d1 + ch : d2 + (ch - half);
+  float ks[8], kh[8], ka[8], kb[8], kc[8], km[8];
+  Vec8<float>::load(scale + ch, ks);
+  Vec8<float>::load(shift + ch, kh);
+  Vec8<float>::load(ca + ch, ka);
+  Vec8<float>::load(cb + ch, kb);
+  Vec8<float>::load(cc + ch, kc);
+  Vec8<float>::load(mean + ch, km);
+  const long row0 = static_cast<long>(blockIdx.x) * rows * APPLY_ROWS + threadIdx.x / c8;
+  Raw8<T> rz[APPLY_ROWS], rh[APPLY_ROWS];
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-      o[j] = fmaf(ca[ch + j], dz[j], fmaf(cb[ch + j], hv[j] - mean[ch + j], cc[ch + j]));
+  for (int r = 0; r < APPLY_ROWS; ++r) {
+    const long row = min(row0 + static_cast<long>(r) * rows, m - 1);
+    rz[r].load(src + row * half);
+    rh[r].load(h + row * c + ch);
+  }
+#pragma unroll
+  for (int r = 0; r < APPLY_ROWS; ++r) {
+    const long row = row0 + static_cast<long>(r) * rows;
+    if (row >= m) break;
+    float dz[8], hv[8], o[8];
+    rz[r].to_f32(dz);
+    rh[r].to_f32(hv);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      if (relu && !(fmaf(ks[j], hv[j], kh[j]) > 0.f)) dz[j] = 0.f;
+      o[j] = fmaf(ka[j], dz[j], fmaf(kb[j], hv[j] - km[j], kc[j]));
+    }
     Vec8<T>::store(dh + row * c + ch, o);
   }
 }
@@ -163,106 +188,167 @@ __global__ __launch_bounds__(256) void scatter2_kernel(const T* src, T* dst1, T*
   }
 }
 
-// One block per image.  c <= 1024, k <= 64.
+// One block per image.  c <= 1024, k <= 64.  Latency-bound (a few KB per image):
+// the pixels are summed 8 channels at a time by all threads, and the softmax runs
+// over the lanes of one wave (one thread did it class by class in fp64, 26 us in
+// all at 128x4x4x512).
 template <typename T>
 __global__ __launch_bounds__(256) void head_kernel(const T* x1, const T* x2, int hw, int c,
                                                    const float* wfc, const float* bfc, int k,
                                                    const int32_t* labels, int n, float* pooled,
                                                    float* dlogits, float* loss_n, T* g1, T* g2) {
-  __shared__ float sp[1024];
+  __shared__ __attribute__((aligned(16))) float part[2048];
+  __shared__ __attribute__((aligned(16))) float sp[1024];
   __shared__ float sl[64];
-  __shared__ float sdp[1024];
   const int img = blockIdx.x;
   const int tid = threadIdx.x;
-  const int half = c / 2;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int half = c / 2, c8 = c / 8;
+  const int groups = 256 / c8;   // pixel groups (c8 <= 128 divides 256)
+  const int ch8 = (tid % c8) * 8, grp = tid / c8;
+  const T* src = ch8 < half ? x1 + static_cast<long>(img) * hw * half + ch8
+                            : x2 + static_cast<long>(img) * hw * half + (ch8 - half);
+  {
+    float acc[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] = 0.f;
+#pragma unroll 4
+    for (int p = grp; p < hw; p += groups) {
+      float v[8];
+      Vec8<T>::load(src + static_cast<long>(p) * half, v);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc[j] += v[j];
+    }
+    Vec8<float>::store(part + tid * 8, acc);   // [group][channel]
+  }
+  __syncthreads();
   for (int ch = tid; ch < c; ch += 256) {
-    const T* src = ch < half ? x1 + static_cast<long>(img) * hw * half + ch
-                             : x2 + static_cast<long>(img) * hw * half + (ch - half);
     float acc = 0.f;
-    for (int p = 0; p < hw; ++p) acc += load1(src + static_cast<long>(p) * half);
+    for (int g = 0; g < groups; ++g) acc += part[g * c + ch];
     const float v = acc / static_cast<float>(hw);
     sp[ch] = v;
     pooled[static_cast<long>(img) * c + ch] = v;
   }
   __syncthreads();
-  const int lane = tid & 63, wave = tid >> 6;
   for (int j = wave; j < k; j += 4) {
     float acc = 0.f;
+#pragma unroll 4
     for (int ch = lane; ch < c; ch += 64) acc += sp[ch] * wfc[static_cast<long>(j) * c + ch];
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
     if (lane == 0) sl[j] = acc + bfc[j];
   }
   __syncthreads();
-  if (tid == 0) {
-    float mx = sl[0];
-    for (int j = 1; j < k; ++j) mx = fmaxf(mx, sl[j]);
-    double se = 0.0;
-    for (int j = 0; j < k; ++j) se += exp(static_cast<double>(sl[j] - mx));
+  if (wave == 0) {
+    const float v = lane < k ? sl[lane] : sl[0];
+    float mx = v;
+    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    const double z = static_cast<double>(v - mx);
+    double se = lane < k ? exp(z) : 0.0;
+    for (int off = 32; off > 0; off >>= 1) se += __shfl_xor(se, off, 64);
     const double lse = log(se);
     const int raw = labels[img];
     const bool valid = raw >= 0 && raw < k;   // an out-of-range label yields a NaN loss
     const int lab = valid ? raw : 0;
-    loss_n[img] = valid ? static_cast<float>(lse - (sl[lab] - mx)) : __int_as_float(0x7fc00000);
-    for (int j = 0; j < k; ++j) {
-      double p = exp(static_cast<double>(sl[j] - mx) - lse);
-      if (j == lab) p -= 1.0;
-      sl[j] = static_cast<float>(p / n);
-      dlogits[static_cast<long>(img) * k + j] = sl[j];
+    if (lane == lab) loss_n[img] = valid ? static_cast<float>(lse - z) : __int_as_float(0x7fc00000);
+    if (lane < k) {
+      const float p = static_cast<float>((exp(z - lse) - (lane == lab ? 1.0 : 0.0)) / n);
+      sl[lane] = p;
+      dlogits[static_cast<long>(img) * k + lane] = p;
     }
   }
   __syncthreads();
-  for (int ch = tid; ch < c; ch += 256) {
-    float acc = 0.f;
-    for (int j = 0; j < k; ++j) acc += sl[j] * wfc[static_cast<long>(j) * c + ch];
-    sdp[ch] = acc / static_cast<float>(hw);
+  // the gradient of every pixel, 8 channels per thread
+  float d[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) d[j] = 0.f;
+#pragma unroll 2
+  for (int q = 0; q < k; ++q) {
+    float w[8];
+    Vec8<float>::load(wfc + static_cast<long>(q) * c + ch8, w);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) d[j] += sl[q] * w[j];
   }
-  __syncthreads();
-  for (long i = tid; i < static_cast<long>(hw) * c; i += 256) {
-    const int p = static_cast<int>(i / c);
-    const int ch = static_cast<int>(i - static_cast<long>(p) * c);
-    T* dst = ch < half ? g1 + (static_cast<long>(img) * hw + p) * half + ch
-                       : g2 + (static_cast<long>(img) * hw + p) * half + (ch - half);
-    store1(dst, sdp[ch]);
-  }
+#pragma unroll
+  for (int j = 0; j < 8; ++j) d[j] = d[j] / static_cast<float>(hw);
+  T* dst = ch8 < half ? g1 + static_cast<long>(img) * hw * half + ch8
+                      : g2 + static_cast<long>(img) * hw * half + (ch8 - half);
+  for (int p = grp; p < hw; p += groups) Vec8<T>::store(dst + static_cast<long>(p) * half, d);
 }
 
+// Blocks [0, k * ceil(c / 32)): 32 channels of one class, 8 groups of images whose
+// sums are added in order; the last block: bias gradients (a wave per class, lanes
+// over images) and the mean loss.  One thread per weight over all images took 46 us
+// at 128 images, 512 channels, 10 classes: a chain of 128 dependent loads.
 __global__ __launch_bounds__(256) void head_grads_kernel(const float* pooled, const float* dlogits,
                                                          const float* loss_n, int n, int c, int k,
                                                          float inv_k, float* gw, float* gb,
                                                          float* loss) {
-  const long i = static_cast<long>(blockIdx.x) * 256 + threadIdx.x;
-  if (i < static_cast<long>(k) * c) {
-    const int j = static_cast<int>(i / c), ch = static_cast<int>(i - static_cast<long>(j) * c);
+  const int tid = threadIdx.x;
+  const int cblocks = (c + 31) / 32;
+  if (static_cast<int>(blockIdx.x) < k * cblocks) {
+    __shared__ float red[8][33];
+    const int j = blockIdx.x / cblocks;
+    const int cl = tid & 31, g = tid >> 5, ch = (blockIdx.x - j * cblocks) * 32 + cl;
     float acc = 0.f;
-    for (int r = 0; r < n; ++r) acc += dlogits[static_cast<long>(r) * k + j] * pooled[static_cast<long>(r) * c + ch];
-    gw[i] += inv_k * acc;
+    if (ch < c) {
+#pragma unroll 8
+      for (int r = g; r < n; r += 8)
+        acc += dlogits[static_cast<long>(r) * k + j] * pooled[static_cast<long>(r) * c + ch];
+    }
+    red[g][cl] = acc;
+    __syncthreads();
+    if (g == 0 && ch < c) {
+#pragma unroll
+      for (int q = 1; q < 8; ++q) acc += red[q][cl];
+      gw[static_cast<long>(j) * c + ch] += inv_k * acc;
+    }
+    return;
   }
-  if (blockIdx.x == 0 && threadIdx.x < k) {
+  const int lane = tid & 63, wave = tid >> 6;
+  for (int j = wave; j < k; j += 4) {
     float acc = 0.f;
-    for (int r = 0; r < n; ++r) acc += dlogits[static_cast<long>(r) * k + threadIdx.x];
-    gb[threadIdx.x] += inv_k * acc;
+    for (int r = lane; r < n; r += 64) acc += dlogits[static_cast<long>(r) * k + j];
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    if (lane == 0) gb[j] += inv_k * acc;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0 && loss != nullptr) {
+  if (wave == 0 && loss != nullptr) {
     double acc = 0.0;
-    for (int r = 0; r < n; ++r) acc += loss_n[r];
-    *loss = static_cast<float>(acc / n);
+    for (int r = lane; r < n; r += 64) acc += loss_n[r];
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    if (lane == 0) *loss = static_cast<float>(acc / n);
   }
 }
 
+// A block owns 32 consecutive weights; its 8 thread rows take interleaved splits,
+// four loads in flight, and the row sums are combined in a fixed order (one thread
+// per weight over all 256 splits took 102 us at 64 x 27 weights).
 __global__ __launch_bounds__(256) void wgrad_reduce_pad_kernel(const float* part, int splits,
                                                                int c_out, int taps, int c_pad,
                                                                int c_real, float inv_k,
                                                                float* grad) {
+  __shared__ float red[8][33];
   const long numel = static_cast<long>(c_out) * taps * c_real;
-  const long i = static_cast<long>(blockIdx.x) * 256 + threadIdx.x;
-  if (i >= numel) return;
-  const int cr = static_cast<int>(i % c_real);
-  const long ot = i / c_real;  // o * taps + tap
-  const long src = ot * c_pad + cr;
-  const long stride = static_cast<long>(c_out) * taps * c_pad;
-  float s = 0.f;
-  for (int t = 0; t < splits; ++t) s += part[t * stride + src];
-  grad[i] += inv_k * s;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  const long i = static_cast<long>(blockIdx.x) * 32 + tx;
+  float acc[4] = {0.f, 0.f, 0.f, 0.f};
+  if (i < numel) {
+    const float* src = part + (i / c_real) * c_pad + i % c_real;
+    const long stride = static_cast<long>(c_out) * taps * c_pad;
+    int t = ty;
+    for (; t + 24 < splits; t += 32) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) acc[u] += src[(t + 8 * u) * stride];
+    }
+    for (; t < splits; t += 8) acc[0] += src[t * stride];
+  }
+  red[ty][tx] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  __syncthreads();
+  if (ty == 0 && i < numel) {
+    float s = 0.f;
+#pragma unroll
+    for (int r = 0; r < 8; ++r) s += red[r][tx];
+    grad[i] += inv_k * s;
+  }
 }
 
 }  // namespace netk
@@ -321,7 +407,8 @@ void split_bwd_apply(int dtype, const void* d1, const void* d2, const void* h,
                      const float* scale, const float* shift, const float* ca, const float* cb,
                      const float* cc, const float* mean, int relu, void* dh, long m, int c,
                      hipStream_t st) {
-  const unsigned g = grid_of(m * (c / 8));
+  const long rows = 256 / (c / 8) * APPLY_ROWS;
+  const unsigned g = static_cast<unsigned>((m + rows - 1) / rows);
   if (dtype == DT_BF16)
     PETRA_LAUNCH(split_bwd_apply_kernel<bf16_t>, dim3(g), dim3(256), 0, st,
                        static_cast<const bf16_t*>(d1), static_cast<const bf16_t*>(d2),
@@ -366,15 +453,15 @@ void head_forward_backward(int dtype, const void* x1, const void* x2, int n, int
 void head_param_grads(const float* pooled, const float* dlogits, const float* loss_n, int n,
                       int c, int k, float inv_k, float* grad_w, float* grad_b, float* loss,
                       hipStream_t st) {
-  const long total = static_cast<long>(k) * c;
-  PETRA_LAUNCH(head_grads_kernel, dim3(grid_of(total)), dim3(256), 0, st, pooled, dlogits,
+  const long blocks = static_cast<long>(k) * ((c + 31) / 32) + 1;
+  PETRA_LAUNCH(head_grads_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, pooled, dlogits,
                      loss_n, n, c, k, inv_k, grad_w, grad_b, loss);
 }
 
 void wgrad_reduce_pad(const float* part, int splits, int c_out, int taps, int c_pad, int c_real,
                       float inv_k, float* grad, hipStream_t st) {
   const long numel = static_cast<long>(c_out) * taps * c_real;
-  PETRA_LAUNCH(wgrad_reduce_pad_kernel, dim3(grid_of(numel)), dim3(256), 0, st, part, splits,
+  PETRA_LAUNCH(wgrad_reduce_pad_kernel, dim3(static_cast<unsigned>((numel + 31) / 32)), dim3(256), 0, st, part, splits,
                      c_out, taps, c_pad, c_real, inv_k, grad);
 }
 
