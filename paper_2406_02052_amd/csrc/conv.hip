@@ -3518,11 +3518,16 @@ int wgrad_tr_plan(int dtype, const WgradArgs& a, int* splits) {
   // 32 / 64 / 128 / 192 / 256 splits per layer, step 1.737 / 1.620 / 1.562 /
   // 1.554 / 1.560 ms); the 16x16 plan (3) a little less (ImageNet32-shaped
   // stage with 16 / 24 / 32 splits per layer: 3.065 / 3.056 / 3.078 ms; 48
-  // splits on another box 3.20 against 3.09 ms with 32).  CIFAR-shaped: 64 /
-  // 96 / 128 splits 0.414 / 0.412 / 0.412 ms, 192 on another box 0.420 ms.
-  // The 8x8 plan (4) in the 4-stage schedule: budget 32 / 48 / 64 / 128 / 192,
-  // tick 3.047 / 3.045 / 3.044 / 3.065 / 3.081 ms.
-  const int budget = (cfg == 2 || cfg == 5 || cfg == 6) ? 192 : cfg == 3 ? 96 : cfg == 4 ? 64 : 128;
+  // splits on another box 3.20 against 3.09 ms with 32).  The others share a
+  // number of workgroups over the layers launched together: plan 1 two per CU
+  // (step of one and two 128x32x32x32 blocks with 256 / 512 / 1024 in all 218 /
+  // 216 / 226 and 411 / 407 / 406 us), plans 3 (64 channels) and 4 one per CU
+  // (backward of 128x16x16x64 with 256 / 384 / 512 in all 162 / 172 / 178 us; tick
+  // of the 4-stage schedule, with its eight layers per stage, 1748 -> 1650 us).
+  const int budget = cfg == 1                                 ? wgrad_share(512, a)
+                     : cfg == 4 || (cfg == 3 && per == 1) ? wgrad_share(256, a)
+                     : cfg == 3                               ? 96
+                                                              : 192;
   if (splits) *splits = std::max(1, std::min(ntiles, budget / per));
   return cfg;
 }

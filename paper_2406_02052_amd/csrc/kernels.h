@@ -60,6 +60,7 @@ struct WgradArgs {
   float* partials;         // [splits][c_out][k_tot]
   int n, h, w, c_in, p, q, c_out, r, s, stride, pad, k_tot, m;
   int rows_per_split, splits;
+  int layers;              // conv layers of the stage: their weight gradients share launches
 };
 
 constexpr int CONV_BM = 128;  // rows per conv output tile (= partial-sum tile)
@@ -106,6 +107,10 @@ int wgrad_tr_plan(int dtype, const WgradArgs& a, int* splits);
 // as for conv_wgrad, partials to its own a.partials); false, with nothing
 // launched, unless that kernel applies to every entry with one configuration.
 constexpr int MAX_WG_GROUP = 16;
+// One layer's part of `total` workgroups for the layers of a launch.
+inline int wgrad_share(int total, const WgradArgs& a) {
+  return total / (a.layers < 1 ? 1 : a.layers < MAX_WG_GROUP ? a.layers : MAX_WG_GROUP);
+}
 struct WgGroupTable {
   int n;
   long block_begin[MAX_WG_GROUP];

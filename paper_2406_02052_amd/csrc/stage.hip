@@ -152,6 +152,7 @@ Stage::Stage(const petra_stage_desc& d) : desc(d) {
       w.n = desc.n; w.h = desc.h; w.w = desc.w; w.p = desc.h; w.q = desc.w;
       w.c_in = cv.cin; w.c_out = cv.cout; w.r = cv.r; w.s = cv.s; w.stride = 1; w.pad = cv.pad;
       w.k_tot = cv.r * cv.s * cv.cin; w.m = static_cast<int>(M);
+      w.layers = static_cast<int>(convs.size());
       w.dh_h = reinterpret_cast<const void*>(16);   // marks dh formed on the fly
       int sp = 0;
       if (wgrad_tr_plan(dt, w, &sp) == 0) defer_wgrad = false;
@@ -280,6 +281,7 @@ void Stage::wgrad_splits(const ConvLayer& cv, int* splits, int* rows_per_split) 
   w.n = desc.n; w.h = desc.h; w.w = desc.w; w.p = desc.h; w.q = desc.w;
   w.c_in = cv.cin; w.c_out = cv.cout; w.r = cv.r; w.s = cv.s; w.stride = 1; w.pad = cv.pad;
   w.k_tot = cv.r * cv.s * cv.cin; w.m = static_cast<int>(M);
+  w.layers = static_cast<int>(convs.size());
   w.dh_h = reinterpret_cast<const void*>(16);   // dh is always formed on the fly (marker)
   int tr_splits = 0;
   if (wgrad_tr_plan(dt, w, &tr_splits) != 0) {
@@ -528,6 +530,7 @@ void Stage::fn_grad(const BwdFn& f, Scratch& s, const BwdFn* next, Scratch* sn, 
     w.c_out = cv.cout; w.r = cv.r; w.s = cv.s; w.stride = 1; w.pad = cv.pad;
     w.k_tot = cv.r * cv.s * cv.cin;
     w.m = static_cast<int>(M);
+    w.layers = static_cast<int>(convs.size());
     wgrad_splits(cv, &w.splits, &w.rows_per_split);
     const double wnumel = static_cast<double>(cv.cout) * w.k_tot;
     TrSeg seg{};

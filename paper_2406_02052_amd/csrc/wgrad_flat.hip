@@ -403,11 +403,12 @@ int wgrad_flat_plan(int dtype, const WgradArgs& a, int* splits) {
   with_plan(dtype, a, [&](auto c) {
     using C = decltype(c);
     fits = C::rows(a.w) <= C::MAX_ROWS && C::lds(a.w) <= MAX_LDS;
-    // 64 workgroups per layer: the four layers of a block, launched together, give
-    // every CU one (28x28 64->64: 49.6 us with 64, 63.7 with 128, 96.4 with 256;
-    // fp32 32x32x32 32->32 34.5, 40.1 and 52.0 us)
+    // the layers of a launch together give every CU one workgroup (four layers of
+    // 28x28 64->64: 49.6 us with 64 each, 63.7 with 128, 96.4 with 256; of fp32
+    // 32x32x32 32->32 34.5, 40.1 and 52.0 us; backward of two blocks of 64x28x28
+    // 549 us with 64 each, 531 with 32)
     const int per = (a.c_out / C::BO) * (a.c_in / C::BC);
-    sp = std::max(1, std::min((a.m + C::P - 1) / C::P, 64 / per));
+    sp = std::max(1, std::min((a.m + C::P - 1) / C::P, wgrad_share(256, a) / per));
   });
   if (!fits) return 0;
   if (splits) *splits = sp;
