@@ -3486,7 +3486,7 @@ void launch_wgrad_bk(const WgradArgs& a, hipStream_t st) {
 // Transposed-read weight gradient: configuration for these arguments (0: not
 // applicable) and the split count it uses.
 int wgrad_tr_plan(int dtype, const WgradArgs& a, int* splits) {
-  // plans 1-6: image sizes with a kernel of their own; else the flattened pixels
+  // plans 1-3, 5, 6: shapes with a kernel of their own; else the flattened pixels
   if (!(dtype == DT_BF16 && a.src2 == nullptr && a.stride == 1 && a.r == a.s &&
         (a.r == 3 || a.r == 1) && a.pad == a.r / 2 && a.p == a.h && a.q == a.w &&
         a.dh_h != nullptr))
@@ -3499,8 +3499,6 @@ int wgrad_tr_plan(int dtype, const WgradArgs& a, int* splits) {
     cfg = a.w == 32 ? 1 : 2; th = 4; tw = a.w; bo = 32; bc = 32;
   } else if (a.r == 3 && a.c_in % 64 == 0 && a.c_out % 64 == 0 && a.w == 16) {
     cfg = 3; th = 8; tw = 16; bo = 64; bc = 64;
-  } else if (a.r == 3 && a.c_in % 64 == 0 && a.c_out % 64 == 0 && a.w == 8) {
-    cfg = 4; th = 8; tw = 8; bo = 64; bc = 64;
   } else if (a.r == 1 && a.c_in == 128 && a.c_out == 32) {
     cfg = 5; th = 1; tw = 128; bo = 32; bc = 128;
   } else if (a.r == 1 && a.c_in == 32 && a.c_out == 128) {
@@ -3521,13 +3519,12 @@ int wgrad_tr_plan(int dtype, const WgradArgs& a, int* splits) {
   // splits on another box 3.20 against 3.09 ms with 32).  The others share a
   // number of workgroups over the layers launched together: plan 1 two per CU
   // (step of one and two 128x32x32x32 blocks with 256 / 512 / 1024 in all 218 /
-  // 216 / 226 and 411 / 407 / 406 us), plans 3 (64 channels) and 4 one per CU
-  // (backward of 128x16x16x64 with 256 / 384 / 512 in all 162 / 172 / 178 us; tick
-  // of the 4-stage schedule, with its eight layers per stage, 1748 -> 1650 us).
-  const int budget = cfg == 1                                 ? wgrad_share(512, a)
-                     : cfg == 4 || (cfg == 3 && per == 1) ? wgrad_share(256, a)
-                     : cfg == 3                               ? 96
-                                                              : 192;
+  // 216 / 226 and 411 / 407 / 406 us), plan 3 with 64 channels one per CU (backward
+  // of 128x16x16x64 with 256 / 384 / 512 in all 162 / 172 / 178 us).
+  const int budget = cfg == 1                 ? wgrad_share(512, a)
+                     : cfg == 3 && per == 1 ? wgrad_share(256, a)
+                     : cfg == 3               ? 96
+                                              : 192;
   if (splits) *splits = std::max(1, std::min(ntiles, budget / per));
   return cfg;
 }
@@ -3582,7 +3579,6 @@ bool tr_map_of(int dtype, const WgradArgs& a, TrMap* out) {
     case 1: mp = tr_map<3, 4, 32, 1, 2, 1, 2, 3, 4>(a); return true;
     case 2: mp = tr_map<3, 4, 56, 1, 2, 1, 2, 3, 1>(a); return true;
     case 3: mp = tr_map<3, 8, 16, 1, 4, 4, 1, 3, 1>(a); return true;
-    case 4: mp = tr_map<3, 8, 8, 1, 4, 4, 1, 1, 1>(a); return true;
     case 5: mp = tr_map<1, 1, 128, 1, 2, 4, 2, 1, 1>(a); return true;
     case 6: mp = tr_map<1, 1, 128, 4, 2, 1, 2, 1, 1>(a); return true;
     case 0: return false;
@@ -3629,7 +3625,6 @@ bool conv_wgrad_tr_group(int dtype, const WgradArgs* args, int n, hipStream_t st
     case 1: launch_wgrad_tr_group<3, 4, 32, 1, 2, 1, 2, 3, 4>(args, n, st); return true;
     case 2: launch_wgrad_tr_group<3, 4, 56, 1, 2, 1, 2, 3, 1>(args, n, st); return true;
     case 3: launch_wgrad_tr_group<3, 8, 16, 1, 4, 4, 1, 3, 1>(args, n, st); return true;
-    case 4: launch_wgrad_tr_group<3, 8, 8, 1, 4, 4, 1, 1, 1>(args, n, st); return true;
     case 5: launch_wgrad_tr_group<1, 1, 128, 1, 2, 4, 2, 1, 1>(args, n, st); return true;
     case 6: launch_wgrad_tr_group<1, 1, 128, 4, 2, 1, 2, 1, 1>(args, n, st); return true;
     case 0: return false;
@@ -3643,7 +3638,6 @@ bool conv_wgrad_tr(int dtype, const WgradArgs& a, hipStream_t st) {
     case 1: launch_wgrad_tr<3, 4, 32, 1, 2, 1, 2, 3, 4>(a, st); return true;
     case 2: launch_wgrad_tr<3, 4, 56, 1, 2, 1, 2, 3, 1>(a, st); return true;
     case 3: launch_wgrad_tr<3, 8, 16, 1, 4, 4, 1, 3, 1>(a, st); return true;
-    case 4: launch_wgrad_tr<3, 8, 8, 1, 4, 4, 1, 1, 1>(a, st); return true;
     case 5: launch_wgrad_tr<1, 1, 128, 1, 2, 4, 2, 1, 1>(a, st); return true;
     case 6: launch_wgrad_tr<1, 1, 128, 4, 2, 1, 2, 1, 1>(a, st); return true;
     case 0: return false;

@@ -15,6 +15,7 @@
 // channels (WO), the input channels (WC), the taps (WT) and, with their sums added
 // in order at the end, the pixels (WP).
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "kernels.h"
@@ -45,12 +46,14 @@ struct Cfg {
   static constexpr int PV = Pix<T>::PV, PO = Pix<T>::pitch(BO), PC = Pix<T>::pitch(BC);
   static constexpr int DG = BO / PV, XG = BC / PV;   // 16-byte pieces per row
   static constexpr int KP = sizeof(T) == 2 ? 32 : 4; // pixels per MFMA
-  static constexpr int D_PT = (P * DG + NT - 1) / NT;
+  // A third of the waves (at least one) load dh and the BN tensor beside it, the
+  // others the input: a wave then holds one side's channel constants and pieces.
+  static constexpr int ND = 64 * (NW * WP >= 3 ? NW * WP / 3 : 1), NX = NT - ND;
+  static constexpr int D_PT = (P * DG + ND - 1) / ND;
   // pieces of the input patch per thread: images up to about 60 pixels wide
-  static constexpr int X_PT = R == 1 ? D_PT * XG / DG + (D_PT * XG % DG != 0)
-                                     : ((P + 122) * XG + NT - 1) / NT;
-  static constexpr int MAX_ROWS = X_PT * NT / XG;
-  static_assert(TPW * WT == R * R && NT % DG == 0 && NT % XG == 0 && P % (KP * WP) == 0, "tile");
+  static constexpr int X_PT = ((P + (R == 3 ? 122 : 0)) * XG + NX - 1) / NX;
+  static constexpr int MAX_ROWS = X_PT * NX / XG;
+  static_assert(TPW * WT == R * R && ND % DG == 0 && NX % XG == 0 && P % (KP * WP) == 0, "tile");
   static int rows(int w) { return P + (R == 3 ? 2 * (w + 1) : 0); }
   static size_t lds(int w) {
     const size_t tile = (static_cast<size_t>(P) * PO + static_cast<size_t>(rows(w) + 1) * PC) * sizeof(T);
@@ -111,68 +114,76 @@ __device__ __forceinline__ void body(const WgradArgs& a, int bx, int by, int bz,
   const __amdgpu_buffer_rsrc_t r_d = make_rsrc(a.dh, static_cast<long>(a.m) * a.c_out * ES);
   const __amdgpu_buffer_rsrc_t r_h = make_rsrc(a.dh_h, static_cast<long>(a.m) * a.c_out * ES);
 
-  // This thread's channels of dh and of the input, and their coefficients.
-  const int og = tid % C::DG, cg = tid % C::XG;
-  float dk[4][PV], xs[PV], xsh[PV];
+  // The wave's side, this thread's channels of it and their coefficients (dh: ca, cb,
+  // cc, mean; input: scale, shift).
+  const bool dside = wave < C::ND / 64;
+  const int lt = dside ? tid : tid - C::ND;
+  const int og = lt % C::DG, cg = lt % C::XG;
+  float k[4][PV];
 #pragma unroll
   for (int j = 0; j < PV; ++j) {
     const int o = o0 + og * PV + j, c = c0 + cg * PV + j;
-    dk[0][j] = a.dh_ca[o];
-    dk[1][j] = a.dh_cb[o];
-    dk[2][j] = a.dh_cc[o];
-    dk[3][j] = a.dh_mean[o];
-    xs[j] = pro ? a.pro_scale[c] : 0.f;
-    xsh[j] = pro ? a.pro_shift[c] : 0.f;
+    k[0][j] = dside ? a.dh_ca[o] : pro ? a.pro_scale[c] : 0.f;
+    k[1][j] = dside ? a.dh_cb[o] : pro ? a.pro_shift[c] : 0.f;
+    k[2][j] = dside ? a.dh_cc[o] : 0.f;
+    k[3][j] = dside ? a.dh_mean[o] : 0.f;
   }
-  u32x4_t rd[C::D_PT], rh[C::D_PT], rx[C::X_PT];
+  constexpr int NR = 2 * C::D_PT > C::X_PT ? 2 * C::D_PT : C::X_PT;
+  u32x4_t r[NR];   // dh and h in turn, or the input
   auto load_tile = [&](int t) {
+    if (dside) {
 #pragma unroll
-    for (int i = 0; i < C::D_PT; ++i) {
-      const int px = (tid + NT * i) / C::DG, m = t * P + px;
-      const uint32_t off = px < P && m < a.m
-                               ? static_cast<uint32_t>((static_cast<long>(m) * a.c_out + o0 + og * PV) * ES)
-                               : BUF_OOB;
-      rd[i] = buf_load16(r_d, off);
-      rh[i] = buf_load16(r_h, off);
-    }
+      for (int i = 0; i < C::D_PT; ++i) {
+        const int px = (lt + C::ND * i) / C::DG, m = t * P + px;
+        const uint32_t off = px < P && m < a.m
+                                 ? static_cast<uint32_t>((static_cast<long>(m) * a.c_out + o0 + og * PV) * ES)
+                                 : BUF_OOB;
+        r[2 * i] = buf_load16(r_d, off);
+        r[2 * i + 1] = buf_load16(r_h, off);
+      }
+    } else {
 #pragma unroll
-    for (int i = 0; i < C::X_PT; ++i) {
-      const int row = (tid + NT * i) / C::XG, m = t * P - halo + row;
-      const uint32_t off = row < rows && m >= 0 && m < a.m
-                               ? static_cast<uint32_t>((static_cast<long>(m) * a.c_in + c0 + cg * PV) * ES)
-                               : BUF_OOB;
-      rx[i] = buf_load16(r_x, off);
+      for (int i = 0; i < C::X_PT; ++i) {
+        const int row = (lt + C::NX * i) / C::XG, m = t * P - halo + row;
+        const uint32_t off = row < rows && m >= 0 && m < a.m
+                                 ? static_cast<uint32_t>((static_cast<long>(m) * a.c_in + c0 + cg * PV) * ES)
+                                 : BUF_OOB;
+        r[i] = buf_load16(r_x, off);
+      }
     }
   };
   auto park_tile = [&](int t, int buf) {
     T* sd = tiles + buf * half_t;
     T* sx = sd + P * PO;
+    if (dside) {
 #pragma unroll
-    for (int i = 0; i < C::D_PT; ++i) {
-      const int px = (tid + NT * i) / C::DG;
-      if (px >= P) continue;
-      float v[PV], h[PV];
-      get16<T>(rd[i], v);
-      get16<T>(rh[i], h);
+      for (int i = 0; i < C::D_PT; ++i) {
+        const int px = (lt + C::ND * i) / C::DG;
+        if (px >= P) continue;
+        float v[PV], h[PV];
+        get16<T>(r[2 * i], v);
+        get16<T>(r[2 * i + 1], h);
 #pragma unroll
-      for (int j = 0; j < PV; ++j) v[j] = fmaf(dk[0][j], v[j], fmaf(dk[1][j], h[j] - dk[3][j], dk[2][j]));
-      u32x4_t w = put16<T>(v);
-      if (t * P + px >= a.m) w = u32x4_t{0u, 0u, 0u, 0u};   // pixels past the end add nothing
-      *reinterpret_cast<u32x4_t*>(sd + px * PO + og * PV) = w;
-    }
-#pragma unroll
-    for (int i = 0; i < C::X_PT; ++i) {
-      const int row = (tid + NT * i) / C::XG;
-      if (row >= rows) continue;
-      u32x4_t w = rx[i];
-      if (pro) {
-        float v[PV];
-        get16<T>(w, v);
-#pragma unroll
-        for (int j = 0; j < PV; ++j) v[j] = fmaxf(fmaf(xs[j], v[j], xsh[j]), 0.f);
-        w = put16<T>(v);
+        for (int j = 0; j < PV; ++j) v[j] = fmaf(k[0][j], v[j], fmaf(k[1][j], h[j] - k[3][j], k[2][j]));
+        u32x4_t w = put16<T>(v);
+        if (t * P + px >= a.m) w = u32x4_t{0u, 0u, 0u, 0u};   // pixels past the end add nothing
+        *reinterpret_cast<u32x4_t*>(sd + px * PO + og * PV) = w;
       }
-      *reinterpret_cast<u32x4_t*>(sx + row * PC + cg * PV) = w;
+    } else {
+#pragma unroll
+      for (int i = 0; i < C::X_PT; ++i) {
+        const int row = (lt + C::NX * i) / C::XG;
+        if (row >= rows) continue;
+        u32x4_t w = r[i];
+        if (pro) {
+          float v[PV];
+          get16<T>(w, v);
+#pragma unroll
+          for (int j = 0; j < PV; ++j) v[j] = fmaxf(fmaf(k[0][j], v[j], k[1][j]), 0.f);
+          w = put16<T>(v);
+        }
+        *reinterpret_cast<u32x4_t*>(sx + row * PC + cg * PV) = w;
+      }
     }
     if constexpr (R == 3) {
       for (int i = tid; i < P; i += NT) {
@@ -341,14 +352,17 @@ void launch(const WgradArgs* args, int n, hipStream_t st) {
 
 // Plans, by type, taps and channel blocks.  A workgroup takes 64, 32 or 16 output
 // and input channels, whatever divides the layer's.  3x3: three waves of taps times
-// four of channels (64 x 64) or of pixels; 1x1: four waves of pixels.  Tiles of 64
-// pixels rather than 128 for 64 x 64: four layers of 64x28x28 64->64 in one launch
-// 49.6 against 58.5 us (registers; the im2col kernel took 4 x 35 us, and a reduce
-// after each), of 128x4x4 256->256 37.4 against 43.9 us.
+// four of channels (64 x 64), or of channels and pixels; 1x1: four waves of pixels.
+// Four layers in one launch, one workgroup per CU: 64x28x28 64->64 33.7 us (im2col:
+// 4 x 35 us and a reduce after each), 128x8x8 128->128 25.7 us (the kernel for 8x8
+// tiles 30.2 us).  Register-bound: tiles of 128 pixels 51.2 and 37.2 us, all waves
+// loading both sides (both sides' constants and pieces in every thread) 49.6 and
+// 37.4 us, all nine taps in one wave 52.1 and 37.0 us.
 template <typename T> struct Plans {
   static constexpr int P1 = sizeof(T) == 2 ? 128 : 64;
-  using C64 = Cfg<T, 3, 1, 4, 4, 1, 3, 1, 64>;
-  using C32 = Cfg<T, 3, 1, 2, 1, 2, 3, sizeof(T) == 2 ? 2 : 4, P1>;
+  using C64 = Cfg<T, 3, 2, 2, 2, 2, 3, 1, 64>;
+  using C32 = std::conditional_t<sizeof(T) == 2, Cfg<T, 3, 1, 2, 2, 1, 3, 2, 128>,
+                                 Cfg<T, 3, 1, 2, 1, 2, 3, 4, 64>>;
   using C16 = Cfg<T, 3, 1, 1, 1, 1, 3, 4, P1>;
   template <int OF, int CF> using One = Cfg<T, 1, 1, OF, 1, CF, 1, 4, P1>;
 };
@@ -404,9 +418,8 @@ int wgrad_flat_plan(int dtype, const WgradArgs& a, int* splits) {
     using C = decltype(c);
     fits = C::rows(a.w) <= C::MAX_ROWS && C::lds(a.w) <= MAX_LDS;
     // the layers of a launch together give every CU one workgroup (four layers of
-    // 28x28 64->64: 49.6 us with 64 each, 63.7 with 128, 96.4 with 256; of fp32
-    // 32x32x32 32->32 34.5, 40.1 and 52.0 us; backward of two blocks of 64x28x28
-    // 549 us with 64 each, 531 with 32)
+    // 28x28 64->64: 33.7 us with 64 each, 41.1 with 128; of fp32 32x32x32 32->32 34.9
+    // and 39.4 us; backward of two blocks of 64x28x28 with 64 each 549 us, with 32 531)
     const int per = (a.c_out / C::BO) * (a.c_in / C::BC);
     sp = std::max(1, std::min((a.m + C::P - 1) / C::P, wgrad_share(256, a) / per));
   });
