@@ -149,7 +149,7 @@ void wgrad_tr_reduce_group(const float* base, const TrSeg* segs, int nseg, float
                            float* grad_base, hipStream_t st);
 
 // BN statistics: partials [tiles][3][c] of (rows, sum h, sum (h - tile mean)^2)
-// combined across tiles with Chan's pairwise formula in fp64 (m rows in all).
+// combined across tiles about one shift in fp64 (m rows in all).
 // Writes scale = gamma*rstd, shift = beta - mean*scale, mean, rstd; when
 // run_mean != nullptr also moves the running statistics (unbiased variance).
 void bn_stats_finalize(const float* partials, int tiles, int c, long m, const float* gamma,
