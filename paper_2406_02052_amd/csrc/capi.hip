@@ -388,6 +388,21 @@ petra_status petra_stage_update(petra_stage* st, void* stream, int32_t* updated)
   return r;
 }
 
+// Small steps run both passes on the caller's stream: three event pairs and the two
+// launches more that split weight gradients take are then most of the host's time,
+// which bounds the step.  The line lies where the passes' own time, one after the other,
+// stays below that: one block (the launches grow with the blocks, the event pairs do
+// not), 3x3 convs of at most 32 channels (bottleneck: 64) and half tensors up to 512 KB.  Step with two streams / one: fp32 8x8x8x16 182 / 141 us, bf16 2x32x32x32
+// 146 / 132, at 512 KB 144 / 139, at 1 MB 142 / 149; bottleneck 16x16x16x64 238 / 199,
+// 64 inner channels 5x14x14x256 228 / 221; but 64 channels 8x16x16 186 / 187, fp32
+// 8x14x14 238 / 270, and 128 channels 4x16x16 269 / 341.
+constexpr long ONE_STREAM_BYTES = 512l << 10;
+static bool one_stream_step(const petra::Stage& s) {
+  const bool neck = s.desc.kind == PETRA_BLOCK_BOTTLENECK;
+  return s.blocks.size() == 1 && s.M * s.desc.c_half * static_cast<long>(s.esz) <= ONE_STREAM_BYTES &&
+         (neck ? s.desc.c_mid <= 64 : s.desc.c_half <= 32);
+}
+
 petra_status petra_stage_step(petra_stage* st, const void* x1, const void* x2, void* y1, void* y2,
                               const void* yb1, const void* yb2, const void* dyb1,
                               const void* dyb2, void* xb1, void* xb2, void* dxb1, void* dxb2,
@@ -412,6 +427,15 @@ petra_status petra_stage_step(petra_stage* st, const void* x1, const void* x2, v
   s.count_backward();
   const bool due = s.update_due();
   hipStream_t main = static_cast<hipStream_t>(stream);
+  if (one_stream_step(s) && !(s.use_graphs && !s.prof.enabled)) {
+    s.forward(x1, x2, y1, y2, main);
+    s.backward(yb1, yb2, dyb1, dyb2, xb1, xb2, dxb1, dxb2, main);
+    if (due) s.update_kernels(main);
+    r = launch_status(s, "petra_stage_step");
+    if (r == PETRA_OK && due) s.mark_updated();
+    if (updated) *updated = (r == PETRA_OK && due) ? 1 : 0;
+    return r;
+  }
   // fork: the forward runs on its own stream after prior work on `main`, the
   // backward on `main` itself; join: the update (and later work on `main`)
   // follow both passes.  With graphs on, each pass replays the graph of its

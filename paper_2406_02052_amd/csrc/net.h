@@ -67,6 +67,7 @@ struct NetStage {
   int wsplits = 0, wrows = 0;
   hipStream_t sf = nullptr, sb = nullptr;
   hipEvent_t ev_f = nullptr, ev_b = nullptr;
+  bool join_f = false, join_b = false;   // streams that this tick gave work to join
   int64_t mem[MEM_COUNT] = {0, 0, 0, 0, 0, 0};
   int64_t bwd_count = 0;            // backward passes (stages without blocks)
 };
