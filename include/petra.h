@@ -218,9 +218,10 @@ petra_status petra_stage_reconstruct_backward(petra_stage* st, const void* y1, c
 petra_status petra_stage_update(petra_stage* st, void* stream, int32_t* updated);
 
 /* One PETRA stage step (Eq. 5): the forward of one micro-batch (x -> y) and
- * the backward of another (yb, dyb -> xb, dxb) run concurrently on two
- * library-owned streams, both reading the current parameters; the update
- * follows both.  All work is ordered after prior work on `stream`, and later
+ * the backward of another (yb, dyb -> xb, dxb), both reading the current
+ * parameters; the update follows both.  They run concurrently, the forward on a
+ * library-owned stream, or one after the other on `stream` where the step is so
+ * small that the event calls would take longer.  All work is ordered after prior work on `stream`, and later
  * work on `stream` is ordered after it.  Aliasing rules of the two calls
  * apply; the forward and backward buffers must not overlap each other. */
 petra_status petra_stage_step(petra_stage* st, const void* x1, const void* x2, void* y1, void* y2,
