@@ -500,6 +500,36 @@ struct Tile { int bm, wk; };
 constexpr Tile TILE[] = {{0, 0}, {64, 4}, {64, 2}, {128, 1}, {64, 1}, {64, 1}, {64, 1}};
 constexpr long MAX_LDS = 60 << 10;   // dynamic LDS of a launch (patch planes)
 
+// Whether the im2col kernels (bf16: conv_staged, fp32 and 16 channels: conv_gemm) take
+// less time.  A workgroup here loads its patch, multiplies and stores once, without
+// overlap, which a few of them per CU hide; with many, the im2col kernels' wider tiles
+// win, which read each pixel for 128 output channels and each weight for 128 pixels.
+// Lines from the time of each conv against theirs, widths 7 to 64, 4k to 400k pixels
+// (64 x 64 tiles; below / above the line):
+//  * 3x3, 64 to 512 channels: 1280 tiles.  64 channels 64k / 98k pixels 0.81 - 1.04 /
+//    0.92 - 1.20, 128 channels 32k / 64k 0.76 - 0.96 / 1.04 - 1.27, 256 channels 16k /
+//    32k below 0.91 / 0.95 - 1.21.  Wider images have more halo rows in a patch: 64
+//    pixels wide, 128 channels, 24k / 32k pixels at most 0.8 / 1.14, hence the bound
+//    on tiles times patch rows.
+//  * 1x1: 960 tiles.  256 -> 64 channels 48k / 80k pixels 0.78 - 0.89 / 0.97 - 1.08.
+//    Forwards to more channels stay: 64 -> 256, 98k pixels, 0.87.  Input gradients with
+//    a residual read it beside the two prologue tensors: 768 tiles, and 512 with the
+//    32-channel tiles.  64 -> 256 16k / 32k pixels 0.86 - 1.06 / 0.94 - 1.21, 128 -> 512
+//    4k / 12k 0.90 / 1.04 - 1.17, 32 -> 64 24k / 64k 0.86 - 0.93 / 1.02 - 1.22.
+//  * 16 input channels, 3x3 forwards, half of a chunk empty: bf16 48k / 98k pixels
+//    0.85 - 0.95 / 1.09 - 1.16, fp32 32k / 64k 0.92 - 0.99 / 1.04 - 1.06.
+//  * fp32 1x1 forwards to 16 channels, a quarter of a tile: 1.0 / 1.5 at 4k / 64k.
+bool im2col_better(int dtype, const ConvArgs& a, int ep) {
+  if (dtype == DT_FP32)
+    return ep == EP_STATS && ((a.r == 1 && a.c_out <= 16) || (a.r == 3 && a.c_in == 16 && a.m > 48 << 10));
+  if (a.c_in == 16) return ep == EP_STATS && a.r == 3 && a.m > 64 << 10;
+  if (a.c_in % 32 != 0) return false;
+  const long tiles = static_cast<long>((a.m + 63) / 64) * ((a.c_out + 63) / 64);
+  if (a.r == 3) return a.c_in > 32 && (tiles > 1280 || tiles * (64 + 2 * (a.w + 1)) > 190000);
+  if (ep == EP_RESID || ep == EP_RESID_STATS) return tiles > (a.c_in == 32 ? 512 : 768);
+  return a.c_in > 32 && (ep != EP_STATS || a.c_out <= a.c_in) && tiles > 960;
+}
+
 Shape shape_of(int dtype, const ConvArgs& a, int ep) {
   const bool fp32 = dtype == DT_FP32;
   if (!(a.src2 == nullptr && (a.r == 3 || a.r == 1) && a.s == a.r && a.stride == 1 &&
@@ -511,6 +541,7 @@ Shape shape_of(int dtype, const ConvArgs& a, int ep) {
   const long esz = fp32 ? 4 : 2;
   // byte offsets of the buffer loads/stores are 32-bit
   if (static_cast<long>(a.m) * std::max(a.c_in, a.c_out) * esz >= static_cast<long>(BUF_OOB)) return F_NO;
+  if (im2col_better(dtype, a, ep)) return F_NO;
   const int chunks = (a.c_in + CK - 1) / CK;
   const long rowb = fp32 ? Lay<float>::ROWB : Lay<bf16_t>::ROWB;
   auto fits = [&](Shape s) {
@@ -524,6 +555,9 @@ Shape shape_of(int dtype, const ConvArgs& a, int ep) {
     if (a.c_out <= 16 && fits(F_N1)) return F_N1;
     return fits(F_N2) ? F_N2 : F_NO;
   }
+  // the pixel waves go over several chunks one after the other: 64 channels 160 x 160
+  // 123 against the im2col kernel's 95 us a forward, 128 channels 128 x 128 191 / 160
+  if (chunks > 1) return F_NO;
   if ((a.m + 127) / 128 < 256 && fits(F_M64)) return F_M64;
   return fits(F_M128) ? F_M128 : F_NO;
 }
