@@ -127,8 +127,14 @@ petra_status petra_stage_destroy(petra_stage* st);
 /* Sizes the caller must allocate: n_params fp32 elements for each of the
  * parameter, gradient-accumulator and momentum buffers; n_tensors parameter
  * tensors; n_bn_channels fp32 elements for each running-statistics array;
- * workspace_bytes of device scratch (compute copies of the weights, one
- * block's intermediates for the forward and for the backward, partial sums). */
+ * workspace_bytes of device scratch (compute copies of the weights, one residual
+ * function's intermediates for the forward and two functions' for the backward,
+ * partial sums).  Beside the copies it does not grow with num_blocks, but for two
+ * kinds of stages, which keep every function's intermediates and four half-width
+ * tensors per inner block through a backward: those that this costs at most 32 MiB,
+ * and bf16 stages all of whose convs have a kernel for their size (3x3 of 32
+ * channels 32 or 56 wide, of multiples of 64 channels 8 or 16 wide; 1x1 of 128 to 32
+ * channels and back). */
 petra_status petra_stage_query(const petra_stage* st, int64_t* n_params, int32_t* n_tensors,
                                int64_t* n_bn_channels, size_t* workspace_bytes);
 petra_status petra_stage_param_info(const petra_stage* st, int32_t index, petra_param_info* out);

@@ -458,7 +458,7 @@ petra_status petra_stage_step(petra_stage* st, const void* x1, const void* x2, v
             ? fail(PETRA_ERR_HIP, std::string("petra_stage_step: ") + hipGetErrorString(ge))
             : launch_status(s, "petra_stage_step");
   } else {
-    if (s.defer_wgrad && s.bwd_streams == 1 && !s.prof.enabled) {
+    if (s.keep_sets && s.bwd_streams == 1 && !s.prof.enabled) {
       // the forward stream is idle once the forward is done: the backward puts
       // most of its deferred weight gradients there (after the forward's
       // launches; the join below covers them)

@@ -118,8 +118,9 @@ struct WgGroupTable {
 };
 bool conv_wgrad_tr_group(int dtype, const WgradArgs* args, int n, hipStream_t st);
 // The same for any image size, bf16 and fp32 (wgrad_flat.hip): wgrad_tr_plan falls
-// back to it, with plan numbers of its own (>= 16).  Plan (0: not applicable) and
+// back to it, with plan numbers of its own (from WGRAD_FLAT_PLAN).  Plan (0: not applicable) and
 // splits, the reduce's map, and one launch of n >= 1 layers of one plan.
+constexpr int WGRAD_FLAT_PLAN = 16;
 int wgrad_flat_plan(int dtype, const WgradArgs& a, int* splits);
 struct TrMap;
 bool wgrad_flat_map(int dtype, const WgradArgs& a, TrMap* out);

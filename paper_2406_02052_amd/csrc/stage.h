@@ -85,13 +85,18 @@ class Stage {
   // ... and the coupling also runs the next function's first conv (1x1 128 -> 32)
   bool couple_next = false;
   ScratchPlan plan_f{};
-  std::vector<ScratchPlan> plan_b;   // 2 sets, or one per residual function (defer_wgrad)
-  // Weight gradients wait until the end of a single-stream backward and run as
-  // one launch per kernel configuration (the first function's only when the
-  // call is not in place); their inputs then stay alive: one scratch set per
-  // function, and the reconstructed inputs and input gradients of blocks 1.. in
-  // their own buffers (4 half-width tensors per block).
+  std::vector<ScratchPlan> plan_b;   // 2 sets, or one per residual function (keep_sets)
+  // Every layer has a weight-gradient kernel that takes several layers: on a single
+  // stream they run as one launch per kernel configuration, at the end of each
+  // residual function or, with keep_sets, of the backward (the first function's at its
+  // end when the call is in place).  With keep_sets their inputs stay alive: one
+  // scratch set per function, and the reconstructed inputs and input gradients of
+  // blocks 1.. in their own buffers (4 half-width tensors per block).
   bool defer_wgrad = false;
+  bool keep_sets = false;
+  // A bound on what a stage's depth may add, for small stages, whose time is that of the
+  // launches: a step of two blocks of 128x4x4x256 (10 MiB) 441 us, 479 without.
+  static constexpr size_t KEEP_BYTES = 32u << 20;
   size_t off_inter = 0;
   size_t off_wpart = 0;
   int64_t wpart_floats = 0;
@@ -110,12 +115,15 @@ class Stage {
   const void* v_wd = nullptr;
   Scratch sf;
   std::vector<Scratch> sb;
-  float* wpart = nullptr;  // weight-gradient split partials, one region per conv layer
+  float* wpart = nullptr;  // weight-gradient split partials
   std::vector<int64_t> wpart_off;       // float offset of each conv layer's region
-  std::vector<TrSeg> pending_reduce;    // reduces deferred to the end of the backward
-  std::vector<WgradArgs> pending_wgrad; // weight gradients deferred to the end of the backward
-  bool defer_cur = false;               // the function being enqueued defers its weight gradients
-  // launch the deferred weight gradients and reduces collected so far on q
+  std::vector<TrSeg> pending_reduce;    // reduces not launched yet
+  std::vector<WgradArgs> pending_wgrad; // weight gradients not launched yet
+  bool defer_cur = false;               // the function being enqueued collects its weight gradients
+  bool flush_fn = false;                // ... and launches them at its end
+  // launch the weight gradients, the reduces, or both collected so far on q
+  void launch_pending_wgrads(hipStream_t q);
+  void launch_pending_reduces(hipStream_t q);
   void flush_deferred(hipStream_t q);
 
   petra_sgd opt{0.1f, 0.9f, 0.0f, 1, 1};
@@ -156,7 +164,7 @@ class Stage {
   // same layout is set (a stashed copy); the update always writes the bound ones.
   void set_view(const float* th, const void* wf, const void* wd) { v_th = th; v_wf = wf; v_wd = wd; }
   void reset_view() { v_th = theta; v_wf = wfwd; v_wd = wdg; }
-  // side (optional, single-stream deferred mode only): a stream that is idle
+  // side (optional, single stream with keep_sets only): a stream that is idle
   // during the second half of the backward; the weight gradients collected by
   // the middle and by the last function run there (one event each), and the
   // caller joins it before the update.
@@ -214,6 +222,7 @@ class Stage {
                 hipStream_t st, const ResidualFn* next = nullptr, Scratch* ns = nullptr);
   bool conv(const ConvArgs& a, int ep, hipStream_t st);
   ConvArgs conv_args(const ConvLayer& cv) const;
+  WgradArgs wgrad_shape(const ConvLayer& cv) const;
   void wgrad_splits(const ConvLayer& cv, int* splits, int* rows_per_split) const;
 };
 

@@ -127,37 +127,12 @@ Stage::Stage(const petra_stage_desc& d) : desc(d) {
       if (ep != EP_STATS) tiles_max = std::max(tiles_max, conv_row_tiles(dt, gb, ep));
     }
   }
-  // each conv layer has its own weight-gradient partials, so their reduces can
-  // wait until the end of the backward and run as one launch
-  int64_t wtot = 0;
-  wpart_off.clear();
-  for (auto& cv : convs) {
-    int sp, rps;
-    wgrad_splits(cv, &sp, &rps);
-    wpart_off.push_back(wtot);
-    wtot += (static_cast<int64_t>(sp) * cv.cout * cv.r * cv.s * cv.cin + 63) / 64 * 64;
-  }
-  wpart_floats = wtot;
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t o = off;
     off = align_up(off + bytes, 256);
     return o;
   };
-  // deferred weight gradients: every layer on the transposed-read kernel
-  {
-    defer_wgrad = blocks.size() >= 1;
-    for (const ConvLayer& cv : convs) {
-      WgradArgs w{};
-      w.n = desc.n; w.h = desc.h; w.w = desc.w; w.p = desc.h; w.q = desc.w;
-      w.c_in = cv.cin; w.c_out = cv.cout; w.r = cv.r; w.s = cv.s; w.stride = 1; w.pad = cv.pad;
-      w.k_tot = cv.r * cv.s * cv.cin; w.m = static_cast<int>(M);
-      w.layers = static_cast<int>(convs.size());
-      w.dh_h = reinterpret_cast<const void*>(16);   // marks dh formed on the fly
-      int sp = 0;
-      if (wgrad_tr_plan(dt, w, &sp) == 0) defer_wgrad = false;
-    }
-  }
   couple_fwd = false;
   if (!blocks.empty() && blocks[0].f.nconv == 3) {
     const ConvLayer& cv = convs[blocks[0].f.conv[2]];
@@ -170,28 +145,66 @@ Stage::Stage(const petra_stage_desc& d) : desc(d) {
     couple_next = couple_fwd && conv1x1_couple_next_ok(dt, a, b);
   }
   const int nfn = 2 * static_cast<int>(blocks.size());
-  plan_b.assign(defer_wgrad ? std::max(2, nfn) : 2, ScratchPlan{});
   off_wfwd = take(static_cast<size_t>(n_conv) * esz);
   off_wdg = take(static_cast<size_t>(n_conv) * esz);
-  std::vector<ScratchPlan*> plans{&plan_f};
-  for (ScratchPlan& pb : plan_b) plans.push_back(&pb);
-  for (ScratchPlan* p : plans) {
+  auto take_set = [&](ScratchPlan& p, bool bwd) {
     for (size_t l = 0; l < 3; ++l)
-      p->h[l] = l >= fn_shapes.size()                        ? 0
-                : p == &plan_f && couple_fwd && l == 2       ? NO_BUF
-                : take(static_cast<size_t>(M) * fn_shapes[l].cout * esz);
-    const bool bwd = p != &plan_f;
-    p->d1[0] = bwd ? take(static_cast<size_t>(M) * cmax * esz) : 0;
-    p->d1[1] = bwd && fn_shapes.size() > 2 ? take(static_cast<size_t>(M) * cmax * esz) : 0;
-    p->part = take(static_cast<size_t>(tiles_max) * 3 * cmax * sizeof(float));
-    p->gpart = bwd ? take(static_cast<size_t>(tiles_max) * 2 * cmax * sizeof(float)) : 0;
-    p->bpart = bwd ? take(static_cast<size_t>(tiles_max) * 2 * cmax * sizeof(float)) : 0;
-    p->bnp = take(static_cast<size_t>(3) * 8 * cmax * sizeof(float));
-    if (p == &plan_f) fwd_need = off;   // compute copies + the forward's scratch set
+      p.h[l] = l >= fn_shapes.size()          ? 0
+               : !bwd && couple_fwd && l == 2 ? NO_BUF
+               : take(static_cast<size_t>(M) * fn_shapes[l].cout * esz);
+    p.d1[0] = bwd ? take(static_cast<size_t>(M) * cmax * esz) : 0;
+    p.d1[1] = bwd && fn_shapes.size() > 2 ? take(static_cast<size_t>(M) * cmax * esz) : 0;
+    p.part = take(static_cast<size_t>(tiles_max) * 3 * cmax * sizeof(float));
+    p.gpart = bwd ? take(static_cast<size_t>(tiles_max) * 2 * cmax * sizeof(float)) : 0;
+    p.bpart = bwd ? take(static_cast<size_t>(tiles_max) * 2 * cmax * sizeof(float)) : 0;
+    p.bnp = take(static_cast<size_t>(3) * 8 * cmax * sizeof(float));
+  };
+  take_set(plan_f, false);
+  fwd_need = off;   // compute copies + the forward's scratch set
+  plan_b.assign(2, ScratchPlan{});
+  for (ScratchPlan& p : plan_b) take_set(p, true);
+
+  // Weight gradients.  keep_sets: those of the whole backward run together, from
+  // scratch sets that all survive it.  A one-block stage does so in the two sets it
+  // has anyway.  With more blocks the scratch grows with them (fp32 128x32x32x32, six
+  // blocks: 965 against 135 MiB), so only those stages do whose every layer has a kernel
+  // of its own size or is 8 pixels wide, and those that it costs KEEP_BYTES at most.
+  // The others alternate between two sets, whatever their depth, and run the weight
+  // gradients of each function at its end: backward of two blocks of 64x28x28x64 540
+  // against 482 us, of fp32 32x32x32x32 360 / 319, of 64x14x14x256 bottlenecks 461 / 423.
+  std::vector<int> plans;
+  bool sized = true;
+  for (const ConvLayer& cv : convs) {
+    plans.push_back(wgrad_tr_plan(dt, wgrad_shape(cv), nullptr));
+    const bool eight = dt == DT_BF16 && desc.w == 8 && cv.r == 3 && cv.cin % 64 == 0 && cv.cout % 64 == 0;
+    sized = sized && (plans.back() < WGRAD_FLAT_PLAN || eight);
+  }
+  defer_wgrad = std::count(plans.begin(), plans.end(), 0) == 0;
+  const size_t inter = (blocks.size() - 1) * 4 * static_cast<size_t>(M) * desc.c_half * esz;
+  const size_t extra = (nfn - 2) * (off - fwd_need) / 2 + inter;
+  keep_sets = defer_wgrad && (sized || extra <= KEEP_BYTES);
+  if (keep_sets) {
+    plan_b.resize(nfn);
+    for (int f = 2; f < nfn; ++f) take_set(plan_b[f], true);
+    off_inter = take(inter);
+  }
+  const size_t fn_convs = fn_shapes.size();
+  // Partials: with keep_sets a region per layer, reduced in one launch at the end;
+  // else a region per layer of one function, reduced at the end of each.
+  wpart_off.clear();
+  wpart_floats = 0;
+  for (size_t i = 0; i < convs.size(); ++i) {
+    const ConvLayer& cv = convs[i];
+    if (!keep_sets && i >= fn_convs) {
+      wpart_off.push_back(wpart_off[i % fn_convs]);
+      continue;
+    }
+    int sp, rps;
+    wgrad_splits(cv, &sp, &rps);
+    wpart_off.push_back(wpart_floats);
+    wpart_floats += (static_cast<int64_t>(sp) * cv.cout * cv.r * cv.s * cv.cin + 63) / 64 * 64;
   }
   off_wpart = take(static_cast<size_t>(wpart_floats) * sizeof(float));
-  if (defer_wgrad && blocks.size() > 1)
-    off_inter = take(static_cast<size_t>(blocks.size() - 1) * 4 * M * desc.c_half * esz);
   ws_need = off;
 }
 
@@ -276,15 +289,19 @@ ConvArgs Stage::conv_args(const ConvLayer& cv) const {
   return a;
 }
 
-void Stage::wgrad_splits(const ConvLayer& cv, int* splits, int* rows_per_split) const {
+WgradArgs Stage::wgrad_shape(const ConvLayer& cv) const {
   WgradArgs w{};
   w.n = desc.n; w.h = desc.h; w.w = desc.w; w.p = desc.h; w.q = desc.w;
   w.c_in = cv.cin; w.c_out = cv.cout; w.r = cv.r; w.s = cv.s; w.stride = 1; w.pad = cv.pad;
   w.k_tot = cv.r * cv.s * cv.cin; w.m = static_cast<int>(M);
   w.layers = static_cast<int>(convs.size());
   w.dh_h = reinterpret_cast<const void*>(16);   // dh is always formed on the fly (marker)
+  return w;
+}
+
+void Stage::wgrad_splits(const ConvLayer& cv, int* splits, int* rows_per_split) const {
   int tr_splits = 0;
-  if (wgrad_tr_plan(dt, w, &tr_splits) != 0) {
+  if (wgrad_tr_plan(dt, wgrad_shape(cv), &tr_splits) != 0) {
     *splits = tr_splits;
     *rows_per_split = 0;
     return;
@@ -511,7 +528,7 @@ void Stage::fn_grad(const BwdFn& f, Scratch& s, const BwdFn* next, Scratch* sn, 
     }
     // weight gradient of conv_l (side stream), from the same dsrc and h_l
     if (wb) PETRA_HIP(hip_status, hipStreamWaitEvent(wst, ev_d, 0));
-    WgradArgs w{};
+    WgradArgs w = wgrad_shape(cv);
     w.dh = dsrc;
     w.dh_h = s.h[l];
     w.dh_ca = s.vec(l, V_CA, cmax);
@@ -526,16 +543,11 @@ void Stage::fn_grad(const BwdFn& f, Scratch& s, const BwdFn* next, Scratch* sn, 
     }
     const int64_t poff = wpart_off[static_cast<size_t>(&cv - convs.data())];
     w.partials = wpart + poff;
-    w.n = desc.n; w.h = desc.h; w.w = desc.w; w.c_in = cv.cin; w.p = desc.h; w.q = desc.w;
-    w.c_out = cv.cout; w.r = cv.r; w.s = cv.s; w.stride = 1; w.pad = cv.pad;
-    w.k_tot = cv.r * cv.s * cv.cin;
-    w.m = static_cast<int>(M);
-    w.layers = static_cast<int>(convs.size());
     wgrad_splits(cv, &w.splits, &w.rows_per_split);
     const double wnumel = static_cast<double>(cv.cout) * w.k_tot;
     TrSeg seg{};
     if (defer_cur) {
-      // launched with the other deferred layers at the end of the backward
+      // launched with the other layers of the function or of the whole backward
       (void)wgrad_tr_segment(dt, w, static_cast<long>(poff), static_cast<long>(cv.w_off), &seg);
       pending_wgrad.push_back(w);
       pending_reduce.push_back(seg);
@@ -546,7 +558,7 @@ void Stage::fn_grad(const BwdFn& f, Scratch& s, const BwdFn* next, Scratch* sn, 
     prof.end(K_CONV_WGRAD, wst, 2.0 * M * wnumel,
              static_cast<double>(esz) * M * (cv.cin + 2.0 * cv.cout) + 4.0 * w.splits * wnumel);
     if (wgrad_tr_segment(dt, w, static_cast<long>(poff), static_cast<long>(cv.w_off), &seg)) {
-      pending_reduce.push_back(seg);   // reduced at the end of the backward
+      pending_reduce.push_back(seg);   // reduced with the others of its group
     } else {
       prof.begin(wst);
       wgrad_reduce(w.partials, w.splits, static_cast<long>(cv.cout) * w.k_tot, inv_k,
@@ -555,6 +567,10 @@ void Stage::fn_grad(const BwdFn& f, Scratch& s, const BwdFn* next, Scratch* sn, 
     }
   }
   if (part == 1) {
+    // the next reconstruction and the next use of this scratch set overwrite what
+    // these read; with one partials region for all functions, the reduce follows
+    if (flush_fn) launch_pending_wgrads(wst);
+    if (!keep_sets) launch_pending_reduces(wst);
     if (rb) PETRA_HIP(hip_status, hipEventRecord(ev_gdone[parity], st));
     if (wb || rs != wst) PETRA_HIP(hip_status, hipEventRecord(ev_wgdone[parity], wst));
   }
@@ -628,9 +644,10 @@ void Stage::backward(const void* y1, const void* y2, const void* dy1, const void
   hipStream_t rs = par && bwd_streams >= 3 ? s_rec : st;
   hipStream_t wst = par && bwd_streams >= 2 ? s_wg : st;
   const bool rb = rs != st, wb = wst != st;
-  // single stream: the weight gradients wait for the end (the first function's
-  // only when its inputs survive the backward)
+  // single stream: the weight gradients are collected and launched together, at the
+  // end of each function or (keep) of the backward
   const bool defer = defer_wgrad && !rb && !wb;
+  const bool keep = defer && keep_sets;
   std::vector<BwdFn> fl;
   const void* c1 = y1;
   const void* c2 = y2;
@@ -639,8 +656,8 @@ void Stage::backward(const void* y1, const void* y2, const void* dy1, const void
   const size_t half = static_cast<size_t>(M) * desc.c_half * esz;
   for (int b = static_cast<int>(blocks.size()) - 1; b >= 0; --b) {
     const Block& blk = blocks[b];
-    // blocks 1.. write to their own buffers when the weight gradients are deferred
-    char* ib = defer && b > 0 ? ws + off_inter + static_cast<size_t>(b - 1) * 4 * half : nullptr;
+    // blocks 1.. write to their own buffers when the weight gradients wait for the end
+    char* ib = keep && b > 0 ? ws + off_inter + static_cast<size_t>(b - 1) * 4 * half : nullptr;
     void* bx1 = ib ? ib : x1;
     void* bx2 = ib ? ib + half : x2;
     void* bdx1 = ib ? ib + 2 * half : dx1;
@@ -653,8 +670,8 @@ void Stage::backward(const void* y1, const void* y2, const void* dy1, const void
   }
   const int nf = static_cast<int>(fl.size());
   std::vector<char> first_done(static_cast<size_t>(nf), 0);   // first conv run by a coupling
-  // scratch set of function f: its own when deferring, else alternating
-  auto S = [&](int f) -> Scratch& { return defer ? sb[f] : sb[f & 1]; };
+  // scratch set of function f: its own when they wait, else alternating
+  auto S = [&](int f) -> Scratch& { return keep ? sb[f] : sb[f & 1]; };
   if (rb || wb) PETRA_HIP(hip_status, hipEventRecord(ev_start, st));
   if (rb) PETRA_HIP(hip_status, hipStreamWaitEvent(rs, ev_start, 0));
   if (wb) PETRA_HIP(hip_status, hipStreamWaitEvent(wst, ev_start, 0));
@@ -681,9 +698,10 @@ void Stage::backward(const void* y1, const void* y2, const void* dy1, const void
     Scratch& sc = S(f);
     Scratch* sn = has_next ? &S(f + 1) : nullptr;
     const void* dsrc = nullptr;
+    defer_cur = defer;
     // the first function's weight gradients read y1 and dy2, which the last
     // function overwrites when the caller runs in place (x1 == y1, dx2 == dy2)
-    defer_cur = defer && (f >= 1 || (x1 != y1 && dx2 != dy2));
+    flush_fn = defer && (!keep || (f == 0 && (x1 == y1 || dx2 == dy2)));
     if (rb) PETRA_HIP(hip_status, hipStreamWaitEvent(st, ev_rec[p], 0));
     fn_grad(fl[f], sc, nx, sn, st, wst, rs, f >= 1, p, 0, &dsrc);
     if (has_next) {
@@ -694,7 +712,7 @@ void Stage::backward(const void* y1, const void* y2, const void* dy1, const void
       if (rb) PETRA_HIP(hip_status, hipEventRecord(ev_rec[p ^ 1], rs));
     }
     fn_grad(fl[f], sc, nx, sn, st, wst, rs, f >= 1, p, 1, &dsrc);
-    if (defer && side != nullptr && ev_side != nullptr && nf >= 2 &&
+    if (keep && side != nullptr && ev_side != nullptr && nf >= 2 &&
         (f + 1 == nf / 2 || f + 1 == nf - 1)) {
       // the weight gradients collected so far on the idle side stream (after
       // the first half and before the last function: one event each)
@@ -709,13 +727,13 @@ void Stage::backward(const void* y1, const void* y2, const void* dy1, const void
       const BwdFn& nx = fl[f + 1];
       // with one scratch set per function (one stream), the reconstruction also
       // runs the first conv of the function after next, whose input it is
-      const bool fuse = defer && !rb && f + 2 < nf && fl[f + 2].u == nx.xrec;
+      const bool fuse = keep && f + 2 < nf && fl[f + 2].u == nx.xrec;
       const bool ran = coupling(*nx.fn, *sn, nx.v, nx.xrec, true, rs,
                                 fuse ? fl[f + 2].fn : nullptr, fuse ? &S(f + 2) : nullptr);
       if (fuse && ran) first_done[f + 2] = 1;
     }
   }
-  defer_cur = false;
+  defer_cur = flush_fn = false;
   // join the side streams
   if (rb) {
     PETRA_HIP(hip_status, hipEventRecord(ev_rec_end, rs));
@@ -729,6 +747,11 @@ void Stage::backward(const void* y1, const void* y2, const void* dy1, const void
 }
 
 void Stage::flush_deferred(hipStream_t st) {
+  launch_pending_wgrads(st);
+  launch_pending_reduces(st);
+}
+
+void Stage::launch_pending_wgrads(hipStream_t st) {
   if (!pending_wgrad.empty()) {
     // one launch per kernel configuration (and per MAX_WG_GROUP layers)
     std::vector<std::pair<int, WgradArgs>> byplan;
@@ -759,7 +782,10 @@ void Stage::flush_deferred(hipStream_t st) {
     }
     pending_wgrad.clear();
   }
-  // the deferred weight-gradient reduces of every layer, in one launch
+}
+
+void Stage::launch_pending_reduces(hipStream_t st) {
+  // the split reduces of the layers launched so far, in one launch
   if (!pending_reduce.empty()) {
     const float inv_k = 1.0f / static_cast<float>(std::max(1, opt.accum_k));
     for (size_t i0 = 0; i0 < pending_reduce.size(); i0 += MAX_TR_SEGS) {

@@ -426,7 +426,7 @@ int wgrad_flat_plan(int dtype, const WgradArgs& a, int* splits) {
   if (!fits) return 0;
   if (splits) *splits = sp;
   // one number per configuration: layers with the same one can share a launch
-  return 16 + (a.r == 3 ? 0 : 1) + 2 * (block_of(a.c_out) + 128 * block_of(a.c_in));
+  return WGRAD_FLAT_PLAN + (a.r == 3 ? 0 : 1) + 2 * (block_of(a.c_out) + 128 * block_of(a.c_in));
 }
 
 bool wgrad_flat_map(int dtype, const WgradArgs& a, TrMap* out) {
