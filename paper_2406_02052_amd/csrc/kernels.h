@@ -60,7 +60,9 @@ struct WgradArgs {
   float* partials;         // [splits][c_out][k_tot]
   int n, h, w, c_in, p, q, c_out, r, s, stride, pad, k_tot, m;
   int rows_per_split, splits;
-  int layers;              // conv layers of the stage: their weight gradients share launches
+  // layers whose weight gradients share this one's launch; 0: none ever, other layers
+  // of the stage having no kernel that takes several
+  int layers;
 };
 
 constexpr int CONV_BM = 128;  // rows per conv output tile (= partial-sum tile)

@@ -86,17 +86,23 @@ class Stage {
   bool couple_next = false;
   ScratchPlan plan_f{};
   std::vector<ScratchPlan> plan_b;   // 2 sets, or one per residual function (keep_sets)
-  // Every layer has a weight-gradient kernel that takes several layers: on a single
-  // stream they run as one launch per kernel configuration, at the end of each
-  // residual function or, with keep_sets, of the backward (the first function's at its
-  // end when the call is in place).  With keep_sets their inputs stay alive: one
-  // scratch set per function, and the reconstructed inputs and input gradients of
-  // blocks 1.. in their own buffers (4 half-width tensors per block).
+  // Every layer has a weight-gradient kernel that takes several layers: they run as one
+  // launch per kernel configuration, at the end of each residual function or, with
+  // keep_sets, of the backward (the first function's at its end when the call is in
+  // place).  With keep_sets their inputs stay alive: one scratch set per function, and
+  // the reconstructed inputs and input gradients of blocks 1.. in their own buffers (4
+  // half-width tensors per block).
   bool defer_wgrad = false;
   bool keep_sets = false;
   // A bound on what a stage's depth may add, for small stages, whose time is that of the
   // launches: a step of two blocks of 128x4x4x256 (10 MiB) 441 us, 479 without.
   static constexpr size_t KEEP_BYTES = 32u << 20;
+  // Per conv: the layers that share a launch with it, on which its number of splits
+  // depends (the same in every stream mode, and so are its bits); whether one has fewer
+  // than it would have by itself: then no stream mode launches them one by one, which
+  // 32 workgroups took 1.2 to 1.7 times as long as layers with splits of their own.
+  std::vector<int> wg_layers;
+  bool few_splits = false;
   size_t off_inter = 0;
   size_t off_wpart = 0;
   int64_t wpart_floats = 0;
@@ -119,6 +125,7 @@ class Stage {
   std::vector<int64_t> wpart_off;       // float offset of each conv layer's region
   std::vector<TrSeg> pending_reduce;    // reduces not launched yet
   std::vector<WgradArgs> pending_wgrad; // weight gradients not launched yet
+  long pending_wgs = 0;                 // workgroups of pending_wgrad
   bool defer_cur = false;               // the function being enqueued collects its weight gradients
   bool flush_fn = false;                // ... and launches them at its end
   // launch the weight gradients, the reduces, or both collected so far on q

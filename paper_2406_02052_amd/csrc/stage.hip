@@ -188,7 +188,17 @@ Stage::Stage(const petra_stage_desc& d) : desc(d) {
     for (int f = 2; f < nfn; ++f) take_set(plan_b[f], true);
     off_inter = take(inter);
   }
-  const size_t fn_convs = fn_shapes.size();
+  // layers of one plan that share a launch
+  wg_layers.assign(convs.size(), defer_wgrad ? 1 : 0);
+  const size_t fn_convs = fn_shapes.size(), group = keep_sets ? convs.size() : fn_convs;
+  for (size_t i = 0; defer_wgrad && i < convs.size(); ++i) {
+    const size_t g0 = i / group * group;
+    int alone = 0, shared = 0;
+    wgrad_tr_plan(dt, wgrad_shape(convs[i]), &alone);
+    wg_layers[i] = static_cast<int>(std::count(plans.begin() + g0, plans.begin() + g0 + group, plans[i]));
+    wgrad_tr_plan(dt, wgrad_shape(convs[i]), &shared);
+    few_splits = few_splits || shared < alone;
+  }
   // Partials: with keep_sets a region per layer, reduced in one launch at the end;
   // else a region per layer of one function, reduced at the end of each.
   wpart_off.clear();
@@ -294,7 +304,8 @@ WgradArgs Stage::wgrad_shape(const ConvLayer& cv) const {
   w.n = desc.n; w.h = desc.h; w.w = desc.w; w.p = desc.h; w.q = desc.w;
   w.c_in = cv.cin; w.c_out = cv.cout; w.r = cv.r; w.s = cv.s; w.stride = 1; w.pad = cv.pad;
   w.k_tot = cv.r * cv.s * cv.cin; w.m = static_cast<int>(M);
-  w.layers = static_cast<int>(convs.size());
+  const size_t i = static_cast<size_t>(&cv - convs.data());
+  w.layers = i < wg_layers.size() ? wg_layers[i] : 1;
   w.dh_h = reinterpret_cast<const void*>(16);   // dh is always formed on the fly (marker)
   return w;
 }
@@ -550,6 +561,7 @@ void Stage::fn_grad(const BwdFn& f, Scratch& s, const BwdFn* next, Scratch* sn, 
       // launched with the other layers of the function or of the whole backward
       (void)wgrad_tr_segment(dt, w, static_cast<long>(poff), static_cast<long>(cv.w_off), &seg);
       pending_wgrad.push_back(w);
+      pending_wgs += static_cast<long>(w.splits) * (w.c_out / seg.mp.bo) * seg.mp.nz;
       pending_reduce.push_back(seg);
       continue;
     }
@@ -638,16 +650,21 @@ void Stage::backward(const void* y1, const void* y2, const void* dy1, const void
   // Residual functions in the order the backward visits them.
   pending_reduce.clear();
   pending_wgrad.clear();
+  pending_wgs = 0;
   // streams: the weight gradients (2+) and the recompute of the next function
   // (3) on side streams; one stream when profiling per launch
   const bool par = s_rec != nullptr && s_wg != nullptr && !prof.enabled;
   hipStream_t rs = par && bwd_streams >= 3 ? s_rec : st;
-  hipStream_t wst = par && bwd_streams >= 2 ? s_wg : st;
+  // layers with few splits each go to the side stream together, others one by one
+  const bool grouped = keep_sets && few_splits;
+  hipStream_t wst = par && bwd_streams >= 2 && !grouped ? s_wg : st;
+  const bool own_side = par && bwd_streams >= 2 && grouped && side == nullptr;
+  if (own_side) side = s_wg;
   const bool rb = rs != st, wb = wst != st;
-  // single stream: the weight gradients are collected and launched together, at the
-  // end of each function or (keep) of the backward
-  const bool defer = defer_wgrad && !rb && !wb;
-  const bool keep = defer && keep_sets;
+  const bool keep = keep_sets && !wb;
+  // beside the chain's own launches: collected and launched together, at the end of
+  // each function or (keep) of the backward
+  const bool defer = defer_wgrad && !wb;
   std::vector<BwdFn> fl;
   const void* c1 = y1;
   const void* c2 = y2;
@@ -712,10 +729,11 @@ void Stage::backward(const void* y1, const void* y2, const void* dy1, const void
       if (rb) PETRA_HIP(hip_status, hipEventRecord(ev_rec[p ^ 1], rs));
     }
     fn_grad(fl[f], sc, nx, sn, st, wst, rs, f >= 1, p, 1, &dsrc);
-    if (keep && side != nullptr && ev_side != nullptr && nf >= 2 &&
-        (f + 1 == nf / 2 || f + 1 == nf - 1)) {
-      // the weight gradients collected so far on the idle side stream (after
-      // the first half and before the last function: one event each)
+    if (keep && side != nullptr && ev_side != nullptr && has_next &&
+        (f + 1 == nf - 1 || (own_side ? pending_wgs >= 128 : f + 1 == nf / 2))) {
+      // the weight gradients collected so far on the side stream: before the last
+      // function, and after the first half (a stream that the forward left idle) or
+      // as soon as they are a workgroup for half of the CUs
       PETRA_HIP(hip_status, hipEventRecord(ev_side, st));
       PETRA_HIP(hip_status, hipStreamWaitEvent(side, ev_side, 0));
       flush_deferred(side);
@@ -727,7 +745,7 @@ void Stage::backward(const void* y1, const void* y2, const void* dy1, const void
       const BwdFn& nx = fl[f + 1];
       // with one scratch set per function (one stream), the reconstruction also
       // runs the first conv of the function after next, whose input it is
-      const bool fuse = keep && f + 2 < nf && fl[f + 2].u == nx.xrec;
+      const bool fuse = keep && !rb && f + 2 < nf && fl[f + 2].u == nx.xrec;
       const bool ran = coupling(*nx.fn, *sn, nx.v, nx.xrec, true, rs,
                                 fuse ? fl[f + 2].fn : nullptr, fuse ? &S(f + 2) : nullptr);
       if (fuse && ran) first_done[f + 2] = 1;
@@ -744,6 +762,10 @@ void Stage::backward(const void* y1, const void* y2, const void* dy1, const void
   // inputs are still intact (each function kept its scratch set and its block's
   // buffers)
   flush_deferred(st);
+  if (own_side) {
+    PETRA_HIP(hip_status, hipEventRecord(ev_side, side));
+    PETRA_HIP(hip_status, hipStreamWaitEvent(st, ev_side, 0));
+  }
 }
 
 void Stage::flush_deferred(hipStream_t st) {
@@ -781,6 +803,7 @@ void Stage::launch_pending_wgrads(hipStream_t st) {
       i0 = i1;
     }
     pending_wgrad.clear();
+    pending_wgs = 0;
   }
 }
 

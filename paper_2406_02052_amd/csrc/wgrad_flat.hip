@@ -54,6 +54,12 @@ struct Cfg {
   static constexpr int X_PT = ((P + (R == 3 ? 122 : 0)) * XG + NX - 1) / NX;
   static constexpr int MAX_ROWS = X_PT * NX / XG;
   static_assert(TPW * WT == R * R && ND % DG == 0 && NX % XG == 0 && P % (KP * WP) == 0, "tile");
+  // Workgroups of a launch, over all its layers: as many as fit on 256 CUs at once, and
+  // two where more, smaller partials cost more.  Weight gradients and reduces of a
+  // backward with 256 / 512 / 768: 64x28x28 64 -> 16 and back 45 / 41 / 47 us, 256 -> 64
+  // (128x28x28) 270 (in 128-pixel tiles, 82 KB of LDS) / 229 / 188, im2col kernels 267;
+  // fp32 64 -> 64 296 / 297 / 303.
+  static constexpr int WGS = R == 3 || sizeof(T) == 4 ? 256 : BO * BC == 64 * 64 ? 768 : 512;
   static int rows(int w) { return P + (R == 3 ? 2 * (w + 1) : 0); }
   static size_t lds(int w) {
     const size_t tile = (static_cast<size_t>(P) * PO + static_cast<size_t>(rows(w) + 1) * PC) * sizeof(T);
@@ -357,14 +363,17 @@ void launch(const WgradArgs* args, int n, hipStream_t st) {
 // 4 x 35 us and a reduce after each), 128x8x8 128->128 25.7 us (the kernel for 8x8
 // tiles 30.2 us).  Register-bound: tiles of 128 pixels 51.2 and 37.2 us, all waves
 // loading both sides (both sides' constants and pieces in every thread) 49.6 and
-// 37.4 us, all nine taps in one wave 52.1 and 37.0 us.
+// 37.4 us, all nine taps in one wave 52.1 and 37.0 us.  bf16 1x1 of 64 x 64 channels:
+// 2 x 2 waves of channels and 64 pixels, so that three workgroups fit on a CU.
 template <typename T> struct Plans {
   static constexpr int P1 = sizeof(T) == 2 ? 128 : 64;
   using C64 = Cfg<T, 3, 2, 2, 2, 2, 3, 1, 64>;
   using C32 = std::conditional_t<sizeof(T) == 2, Cfg<T, 3, 1, 2, 2, 1, 3, 2, 128>,
                                  Cfg<T, 3, 1, 2, 1, 2, 3, 4, 64>>;
   using C16 = Cfg<T, 3, 1, 1, 1, 1, 3, 4, P1>;
-  template <int OF, int CF> using One = Cfg<T, 1, 1, OF, 1, CF, 1, 4, P1>;
+  template <int OF, int CF> using One =
+      std::conditional_t<sizeof(T) == 2 && OF == 4 && CF == 4, Cfg<T, 1, 2, 2, 2, 2, 1, 1, 64>,
+                         Cfg<T, 1, 1, OF, 1, CF, 1, 4, P1>>;
 };
 
 // Calls f with the configuration of a plan (block sizes bo, bc in channels).
@@ -412,16 +421,20 @@ int wgrad_flat_plan(int dtype, const WgradArgs& a, int* splits) {
   const long esz = dtype == DT_BF16 ? 2 : 4;
   // byte offsets of the buffer loads are 32-bit
   if (static_cast<long>(a.m) * std::max(a.c_in, a.c_out) * esz >= static_cast<long>(BUF_OOB)) return 0;
+  // By themselves the 1x1 layers of many pixels are no faster than the im2col kernel,
+  // and slower beside other streams' work (16x64x64 256 -> 64 and back, 64 wide: 4k
+  // pixels 77 against 117 us a backward, 64k 206 / 203, a step of two blocks 1416 / 1406)
+  if (a.layers == 0 && a.r == 1 && a.m > 48 << 10) return 0;
   bool fits = false;
   int sp = 1;
   with_plan(dtype, a, [&](auto c) {
     using C = decltype(c);
     fits = C::rows(a.w) <= C::MAX_ROWS && C::lds(a.w) <= MAX_LDS;
-    // the layers of a launch together give every CU one workgroup (four layers of
-    // 28x28 64->64: 33.7 us with 64 each, 41.1 with 128; of fp32 32x32x32 32->32 34.9
-    // and 39.4 us; backward of two blocks of 64x28x28 with 64 each 549 us, with 32 531)
+    // one workgroup per CU of the 3x3 plans (four layers of 28x28 64->64: 33.7 us with
+    // 64 each, 41.1 with 128; of fp32 32x32x32 32->32 34.9 and 39.4 us; backward of two
+    // blocks of 64x28x28 as one launch with 64 each 549 us, with 32 531)
     const int per = (a.c_out / C::BO) * (a.c_in / C::BC);
-    sp = std::max(1, std::min((a.m + C::P - 1) / C::P, wgrad_share(256, a) / per));
+    sp = std::max(1, std::min((a.m + C::P - 1) / C::P, wgrad_share(C::WGS, a) / per));
   });
   if (!fits) return 0;
   if (splits) *splits = sp;
