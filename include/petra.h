@@ -189,8 +189,8 @@ petra_status petra_stage_forward(petra_stage* st, const void* x1, const void* x2
  * bits, that needs no workspace.  Its scratch -- the compute copies of the
  * conv weights, refreshed from params on every call, and one residual
  * function's pre-BN tensors and BN partial sums -- lives in a static device
- * array of PETRA_STATIC_SCRATCH_BYTES that the library holds on each device it
- * runs on until the process ends.  The call allocates nothing and always
+ * array of PETRA_STATIC_SCRATCH_BYTES (and 6 MiB more for partial sums beyond it)
+ * that the library holds on each device it runs on until the process ends.  The call allocates nothing and always
  * launches directly (no graph cache, no timing events).  The handle may be
  * bound with workspace = NULL and workspace_bytes = 0 (every other compute
  * call then returns PETRA_ERR_WORKSPACE).  PETRA_ERR_WORKSPACE when the stage's

@@ -161,25 +161,32 @@ uintptr_t P(const void* p) { return reinterpret_cast<uintptr_t>(p); }
 // its name as an address: the device address comes from hipGetSymbolAddress,
 // once per device, and is kept in g_scratch below.
 static __device__ __align__(256) unsigned char scratch[PETRA_STATIC_SCRATCH_BYTES];
+// Partial-sum rows of a forward that fits the array but for the finer rows of the
+// convs on flattened pixels.  A row is 3 fp32 values per channel for 64 pixels, which
+// hold at least 2 bytes per channel in the array (or for 128 pixels with 1 byte, where
+// a fused coupling keeps 64 of 128 channels): at most 6/64 of it.
+constexpr size_t ROWS_BYTES = PETRA_STATIC_SCRATCH_BYTES / 64 * 6;
+static __device__ __align__(256) unsigned char scratch_rows[ROWS_BYTES];
 
 namespace {
 
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;
-void* g_scratch[kMaxDevices] = {};
+struct StaticScratch { void* main; void* rows; };
+StaticScratch g_scratch[kMaxDevices] = {};
 
-// Device address of the current device's copy of `scratch`.
-hipError_t static_scratch(void** out) {
+// Device addresses of the current device's copies of `scratch` and `scratch_rows`.
+hipError_t static_scratch(StaticScratch* out) {
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
   std::lock_guard<std::mutex> lock(g_scratch_mu);
-  if (g_scratch[dev] == nullptr) {
-    void* ptr = nullptr;
-    e = hipGetSymbolAddress((void**)&ptr, HIP_SYMBOL(scratch));
-    if (e != hipSuccess) return e;
-    g_scratch[dev] = ptr;
+  if (g_scratch[dev].main == nullptr) {
+    StaticScratch s{};
+    if ((e = hipGetSymbolAddress(&s.main, HIP_SYMBOL(scratch))) != hipSuccess) return e;
+    if ((e = hipGetSymbolAddress(&s.rows, HIP_SYMBOL(scratch_rows))) != hipSuccess) return e;
+    g_scratch[dev] = s;
   }
   *out = g_scratch[dev];
   return hipSuccess;
@@ -342,18 +349,20 @@ petra_status petra_stage_forward_noalloc(petra_stage* st, const void* x1, const 
   if (!s.bound()) return fail(PETRA_ERR_STATE, "stage buffers not bound");
   petra_status r;
   if ((r = check_fwd(s, x1, x2, y1, y2))) return r;
-  if (s.fwd_need > static_cast<size_t>(PETRA_STATIC_SCRATCH_BYTES))
+  const bool own_rows = s.fwd_need > static_cast<size_t>(PETRA_STATIC_SCRATCH_BYTES);
+  if (s.fwd_counted > static_cast<size_t>(PETRA_STATIC_SCRATCH_BYTES) ||
+      (own_rows && s.fwd_rows > ROWS_BYTES))
     return fail(PETRA_ERR_WORKSPACE,
                 "petra_stage_forward_noalloc: the stage's forward needs " +
-                    std::to_string(s.fwd_need) + " bytes of scratch; the static scratch holds " +
+                    std::to_string(s.fwd_counted) + " bytes of scratch; the static scratch holds " +
                     std::to_string(static_cast<size_t>(PETRA_STATIC_SCRATCH_BYTES)));
   if ((r = check_hip("before petra_stage_forward_noalloc"))) return r;
-  void* base = nullptr;
-  const hipError_t e = static_scratch(&base);
+  StaticScratch mem{};
+  const hipError_t e = static_scratch(&mem);
   if (e != hipSuccess)
     return fail(PETRA_ERR_HIP, std::string("petra_stage_forward_noalloc: scratch address: ") +
                                    hipGetErrorString(e));
-  s.forward_on(static_cast<char*>(base), x1, x2, y1, y2, static_cast<hipStream_t>(stream));
+  s.forward_on(static_cast<char*>(mem.main), own_rows ? mem.rows : nullptr, x1, x2, y1, y2, static_cast<hipStream_t>(stream));
   return launch_status(s, "petra_stage_forward_noalloc");
 }
 

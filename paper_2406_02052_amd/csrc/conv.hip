@@ -3719,14 +3719,14 @@ bool conv1x1_couple(int dtype, const ConvArgs& a, const float* scale, const floa
   return true;
 }
 
-int conv_row_tiles(int dtype, const ConvArgs& a, int ep) {
+int conv_row_tiles(int dtype, const ConvArgs& a, int ep, bool flat) {
   if (use_1x1(dtype, a, ep)) return conv1x1_grid(a);
   if (use_img(dtype, a)) return a.n;
   const C32Shape c32 = conv32_shape(dtype, a);
   if (c32.th != 0) return c32.grid;
   const HaloShape hs = halo_shape(dtype, a);
   if (hs.tw != 0) return ((a.w + hs.tw - 1) / hs.tw) * ((a.h + hs.th - 1) / hs.th) * a.n;
-  if (const int ft = conv_flat_tiles(dtype, a, ep)) return ft;
+  if (const int ft = flat ? conv_flat_tiles(dtype, a, ep) : 0) return ft;
   int bm = CONV_BM;
   if (use_staged(dtype, a)) bm = a.c_out <= 32 ? 256 : 128;
   return (a.m + bm - 1) / bm;

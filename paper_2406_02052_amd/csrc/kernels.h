@@ -72,8 +72,8 @@ constexpr int CONV_BM = 128;  // rows per conv output tile (= partial-sum tile)
 // PRO_BWD).
 bool conv_gemm(int dtype, const ConvArgs& a, int ep, hipStream_t st);
 // Number of partial-sum rows (output row tiles) conv_gemm writes for these
-// arguments and epilogue.
-int conv_row_tiles(int dtype, const ConvArgs& a, int ep);
+// arguments and epilogue; without `flat`, those it would write without conv_flat.
+int conv_row_tiles(int dtype, const ConvArgs& a, int ep, bool flat = true);
 // Convolution on flattened pixels, any image size (conv_flat.hip): conv_gemm takes
 // it where no kernel for a particular size applies.  Its number of partial-sum rows
 // (0: it does not apply), and the launch (false, with nothing launched, then).

@@ -42,11 +42,11 @@ struct Block {
 struct Scratch {
   void* h[3] = {nullptr, nullptr, nullptr};  // pre-BN conv outputs of the function
   void* d1[2] = {nullptr, nullptr};          // masked gradients dz of inner layers (backward)
-  float* part = nullptr;                     // BN statistic partials of the recompute [tiles][3][c]
-  float* gpart = nullptr;                    // BN-backward partials of the last BN [tiles][2][c]
-  float* bpart = nullptr;                    // BN-backward partials of an inner BN [tiles][2][c]
+  // Partial-sum rows, one pass's after another's: BN statistics of the recompute
+  // [tiles][3][c], then BN-backward sums of the last BN and of each inner one [tiles][2][c].
+  float* part = nullptr;
   float* bnp = nullptr;                      // per layer: scale, shift, mean, rstd, ca, cb, cc
-  int gtiles = 0;                            // tile count of gpart (host side, set at enqueue)
+  int gtiles = 0;                            // tile count of part (host side, set at enqueue)
   float* vec(int layer, int which, int cmax) const { return bnp + (layer * 8 + which) * cmax; }
 };
 
@@ -72,9 +72,12 @@ class Stage {
   // Workspace plan (byte offsets).
   size_t ws_need = 0;
   size_t fwd_need = 0;   // leading workspace bytes the forward uses (copies + scratch set)
+  // ... its partial-sum rows, the last of them, and the bytes that petra_stage_forward_noalloc's
+  // limit counts
+  size_t fwd_rows = 0, fwd_counted = 0;
   size_t off_wfwd = 0, off_wdg = 0;
   struct ScratchPlan {
-    size_t h[3], d1[2], part, gpart, bpart, bnp;
+    size_t h[3], d1[2], part, bnp;
   };
   static constexpr size_t NO_BUF = ~static_cast<size_t>(0);   // a buffer the set does not hold
   // Residual functions whose last conv is the bf16 1x1 32 -> 128: every
@@ -157,8 +160,9 @@ class Stage {
   // Kernel sequences (enqueue only; no host-side bookkeeping).
   void forward(const void* x1, const void* x2, void* y1, void* y2, hipStream_t st);
   // The forward with its compute copies and scratch set laid out at `base` as in
-  // the first fwd_need bytes of the workspace (the copies refreshed first).
-  void forward_on(char* base, const void* x1, const void* x2, void* y1, void* y2,
+  // the first fwd_need bytes of the workspace (the copies refreshed first); rows: its
+  // partial-sum rows elsewhere.
+  void forward_on(char* base, void* rows, const void* x1, const void* x2, void* y1, void* y2,
                   hipStream_t st);
   // The forward on a given scratch set (the backward's sb[0] for a recompute that
   // runs on the backward's stream while another forward may be in flight).

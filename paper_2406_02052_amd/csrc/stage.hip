@@ -110,9 +110,12 @@ Stage::Stage(const petra_stage_desc& d) : desc(d) {
     max_wnumel = std::max<int64_t>(max_wnumel, static_cast<int64_t>(cv.cout) * cv.r * cv.s * cv.cin);
   }
 
-  // Workspace plan.
-  int tiles_max = 1;
+  // Workspace plan.  Partial-sum rows of the forward and of any pass, and as many as
+  // the latter were with the kernels for any image size alone, whose rows are wider:
+  // petra_stage_forward_noalloc's limit is counted with those.
+  int tiles_max = 1, tiles_fwd = 1, tiles_wide = 1;
   for (auto& s : fn_shapes) tiles_max = std::max(tiles_max, ew_tiles(M, s.cout));
+  tiles_wide = tiles_max;
   for (const ConvLayer& cv : convs) {
     ConvArgs f = conv_args(cv);
     f.c_in = cv.cin; f.c_out = cv.cout; f.k_tot = cv.r * cv.s * cv.cin;
@@ -121,10 +124,13 @@ Stage::Stage(const petra_stage_desc& d) : desc(d) {
     // the input-gradient convs run with the BN-backward prologue
     ConvArgs gb = g;
     gb.pro_h = reinterpret_cast<const void*>(16);
+    tiles_fwd = std::max(tiles_fwd, conv_row_tiles(dt, f, EP_STATS));
     for (int ep : {EP_STATS, EP_MASK, EP_RESID_STATS}) {
-      tiles_max = std::max(tiles_max, conv_row_tiles(dt, f, ep));
-      tiles_max = std::max(tiles_max, conv_row_tiles(dt, g, ep));
-      if (ep != EP_STATS) tiles_max = std::max(tiles_max, conv_row_tiles(dt, gb, ep));
+      for (const ConvArgs* a : {&f, &g, &gb}) {
+        if (ep == EP_STATS && a == &gb) continue;
+        tiles_max = std::max(tiles_max, conv_row_tiles(dt, *a, ep));
+        tiles_wide = std::max(tiles_wide, conv_row_tiles(dt, *a, ep, false));
+      }
     }
   }
   size_t off = 0;
@@ -147,6 +153,7 @@ Stage::Stage(const petra_stage_desc& d) : desc(d) {
   const int nfn = 2 * static_cast<int>(blocks.size());
   off_wfwd = take(static_cast<size_t>(n_conv) * esz);
   off_wdg = take(static_cast<size_t>(n_conv) * esz);
+  auto rows_bytes = [&](int tiles) { return static_cast<size_t>(tiles) * 3 * cmax * sizeof(float); };
   auto take_set = [&](ScratchPlan& p, bool bwd) {
     for (size_t l = 0; l < 3; ++l)
       p.h[l] = l >= fn_shapes.size()          ? 0
@@ -154,13 +161,14 @@ Stage::Stage(const petra_stage_desc& d) : desc(d) {
                : take(static_cast<size_t>(M) * fn_shapes[l].cout * esz);
     p.d1[0] = bwd ? take(static_cast<size_t>(M) * cmax * esz) : 0;
     p.d1[1] = bwd && fn_shapes.size() > 2 ? take(static_cast<size_t>(M) * cmax * esz) : 0;
-    p.part = take(static_cast<size_t>(tiles_max) * 3 * cmax * sizeof(float));
-    p.gpart = bwd ? take(static_cast<size_t>(tiles_max) * 2 * cmax * sizeof(float)) : 0;
-    p.bpart = bwd ? take(static_cast<size_t>(tiles_max) * 2 * cmax * sizeof(float)) : 0;
     p.bnp = take(static_cast<size_t>(3) * 8 * cmax * sizeof(float));
+    // one buffer for the rows of all passes: each is reduced before the next is written
+    p.part = take(rows_bytes(bwd ? tiles_max : tiles_fwd));
   };
   take_set(plan_f, false);
   fwd_need = off;   // compute copies + the forward's scratch set
+  fwd_rows = rows_bytes(tiles_fwd);
+  fwd_counted = plan_f.part + align_up(rows_bytes(tiles_wide), 256);
   plan_b.assign(2, ScratchPlan{});
   for (ScratchPlan& p : plan_b) take_set(p, true);
 
@@ -240,8 +248,6 @@ Scratch Stage::carve(const ScratchPlan& p, char* base, bool bwd) const {
   s.d1[0] = bwd ? base + p.d1[0] : nullptr;
   s.d1[1] = bwd && nl > 2 ? base + p.d1[1] : nullptr;
   s.part = reinterpret_cast<float*>(base + p.part);
-  s.gpart = bwd ? reinterpret_cast<float*>(base + p.gpart) : nullptr;
-  s.bpart = bwd ? reinterpret_cast<float*>(base + p.bpart) : nullptr;
   s.bnp = reinterpret_cast<float*>(base + p.bnp);
   return s;
 }
@@ -448,7 +454,7 @@ bool Stage::conv(const ConvArgs& a, int ep, hipStream_t st) {
 // Gradient chain of one residual function (enqueue only), in two parts so the
 // recompute of the next function can be enqueued between them: part 0 is the
 // BN_L-backward coefficients and the layers L..1, part 1 the first layer.  s
-// holds the function's recomputed h and BN statistics and, in gpart, the
+// holds the function's recomputed h and BN statistics and, in part, the
 // BN_L-backward partials of its output gradient d.  next/sn: the function
 // visited next (recompute enqueued before part 1), whose BN_L-backward partials
 // the first-layer conv emits.  Each layer's input-gradient conv is enqueued
@@ -465,7 +471,7 @@ void Stage::fn_grad(const BwdFn& f, Scratch& s, const BwdFn* next, Scratch* sn, 
     const ConvLayer& cv = convs[fn.conv[L]];
     const BnLayer& bn = bns[cv.bn];
     prof.begin(st);
-    bn_bwd_finalize(s.gpart, s.gtiles, cv.cout, M, v_th + bn.g_off, s.vec(L, V_MEAN, cmax),
+    bn_bwd_finalize(s.part, s.gtiles, cv.cout, M, v_th + bn.g_off, s.vec(L, V_MEAN, cmax),
                     s.vec(L, V_RSTD, cmax), inv_k, grad + bn.g_off, grad + bn.b_off,
                     s.vec(L, V_CA, cmax), s.vec(L, V_CB, cmax), s.vec(L, V_CC, cmax), st);
     prof.end(K_BN_BWD_FINALIZE, st, 0.0, 8.0 * s.gtiles * cv.cout);
@@ -502,13 +508,13 @@ void Stage::fn_grad(const BwdFn& f, Scratch& s, const BwdFn* next, Scratch* sn, 
       a.ep_shift = s.vec(l - 1, V_SHIFT, cmax);
       a.ep_mean = s.vec(l - 1, V_MEAN, cmax);
       a.ep_rstd = s.vec(l - 1, V_RSTD, cmax);
-      a.partials = s.bpart;
+      a.partials = s.part;
       const int tiles_conv = conv_row_tiles(dt, a, EP_MASK);
       prof.begin(st);
       conv(a, EP_MASK, st);
       prof.end(K_CONV_DGRAD, st, 2.0 * M * cv.cin * a.k_tot, dbytes);
       prof.begin(st);
-      bn_bwd_finalize(s.bpart, tiles_conv, lo.cout, M, v_th + bl.g_off, s.vec(l - 1, V_MEAN, cmax),
+      bn_bwd_finalize(s.part, tiles_conv, lo.cout, M, v_th + bl.g_off, s.vec(l - 1, V_MEAN, cmax),
                       s.vec(l - 1, V_RSTD, cmax), inv_k, grad + bl.g_off, grad + bl.b_off,
                       s.vec(l - 1, V_CA, cmax), s.vec(l - 1, V_CB, cmax),
                       s.vec(l - 1, V_CC, cmax), st);
@@ -526,7 +532,7 @@ void Stage::fn_grad(const BwdFn& f, Scratch& s, const BwdFn* next, Scratch* sn, 
         a.ep_h = sn->h[NL];
         a.ep_mean = sn->vec(NL, V_MEAN, cmax);
         a.ep_rstd = sn->vec(NL, V_RSTD, cmax);
-        a.partials = sn->gpart;
+        a.partials = sn->part;
         sn->gtiles = conv_row_tiles(dt, a, EP_RESID_STATS);
         prof.begin(st);
         conv(a, EP_RESID_STATS, st);
@@ -592,13 +598,14 @@ void Stage::forward(const void* x1, const void* x2, void* y1, void* y2, hipStrea
   forward_with(x1, x2, y1, y2, sf, st);
 }
 
-void Stage::forward_on(char* base, const void* x1, const void* x2, void* y1, void* y2,
+void Stage::forward_on(char* base, void* rows, const void* x1, const void* x2, void* y1, void* y2,
                        hipStream_t st) {
   void* wf = base + off_wfwd;
   void* wd = base + off_wdg;
   // the compute copies of the current master parameters, then the forward
   refresh_weights(dt, theta, segs, max_wnumel, wf, wd, st);
   Scratch s = carve(plan_f, base, false);
+  if (rows != nullptr) s.part = static_cast<float*>(rows);
   const float* th0 = v_th;
   const void* wf0 = v_wf;
   const void* wd0 = v_wd;
@@ -703,7 +710,7 @@ void Stage::backward(const void* y1, const void* y2, const void* dy1, const void
     prof.begin(rs);
     combine_bwd(dt, fl[0].v, s0.h[L], fl[0].d, s0.vec(L, V_SCALE, cmax),
                 s0.vec(L, V_SHIFT, cmax), s0.vec(L, V_MEAN, cmax),
-                s0.vec(L, V_RSTD, cmax), fl[0].xrec, s0.gpart, M, c, rs);
+                s0.vec(L, V_RSTD, cmax), fl[0].xrec, s0.part, M, c, rs);
     prof.end(K_COMBINE_BWD, rs, 0.0, 4.0 * M * c * esz);
     s0.gtiles = ew_tiles(M, c);
     if (rb) PETRA_HIP(hip_status, hipEventRecord(ev_rec[0], rs));

@@ -96,3 +96,32 @@ def test_forward_noalloc_rejects_a_stage_beyond_the_scratch():
     rc = fwd_noalloc(st.handle, *(t.data_ptr() for t in a), None)
     assert L.STATUS[rc] == "PETRA_ERR_WORKSPACE"
     assert "static scratch" in L.load().petra_last_error().decode()
+
+
+B = synth.CIFAR_STAGE.with_(blocks=1)
+
+
+@pytest.mark.parametrize("wl", [B.with_(n=324, h=28, w=28, c_half=64),
+                                B.with_(n=631, h=14, w=14, c_half=128),
+                                synth.BLOCK_FP32.with_(n=661, h=28, w=28),
+                                synth.BLOCK_FP32.with_(n=252, h=32, w=32, c_half=32),
+                                synth.IMAGENET_BOTTLENECK_STAGE.with_(n=1250, h=20, w=20, blocks=1)],
+                         ids=["bf16_28x28x64", "bf16_14x14x128", "fp32_28x28x16", "fp32_32x32x32",
+                              "bf16_bottleneck_20x20x128"])
+def test_forward_noalloc_limit(wl):
+    """The first batch that the array does not hold, with a partial-sum row per 128 pixels
+    (256 for up to 32 channels) of the convs without a kernel of their size, is refused and
+    the last that it holds runs, also where the convs write more rows than that."""
+    from paper_2406_02052_amd import Stage
+    from paper_2406_02052_amd import _lib as L
+
+    _, fwd_noalloc = _lib()
+    print(f"noalloc limit case {wl.name} n={wl.n} h={wl.h} c={wl.c_half} {wl.dtype}", flush=True)
+    st = Stage(wl.n, wl.h, wl.w, wl.c_half, wl.blocks, wl.kind, wl.dtype, c_mid=wl.c_mid)
+    a = [st.act() for _ in range(4)]
+    rc = fwd_noalloc(st.handle, *(t.data_ptr() for t in a), None)
+    assert L.STATUS[rc] == "PETRA_ERR_WORKSPACE"
+    del st, a
+    want, got = _forward_both(wl.with_(n=wl.n - 1))
+    for x, y in zip(want, got):
+        assert np.array_equal(x, y)
