@@ -401,15 +401,17 @@ petra_status petra_stage_update(petra_stage* st, void* stream, int32_t* updated)
 // launches more that split weight gradients take are then most of the host's time,
 // which bounds the step.  The line lies where the passes' own time, one after the other,
 // stays below that: one block (the launches grow with the blocks, the event pairs do
-// not), 3x3 convs of at most 32 channels (bottleneck: 64) and half tensors up to 512 KB.  Step with two streams / one: fp32 8x8x8x16 182 / 141 us, bf16 2x32x32x32
-// 146 / 132, at 512 KB 144 / 139, at 1 MB 142 / 149; bottleneck 16x16x16x64 238 / 199,
-// 64 inner channels 5x14x14x256 228 / 221; but 64 channels 8x16x16 186 / 187, fp32
-// 8x14x14 238 / 270, and 128 channels 4x16x16 269 / 341.
+// not), 3x3 convs of at most 32 channels (bf16 bottlenecks: 64) and half tensors up to
+// 512 KB.  Step with two streams / one: fp32 8x8x8x16 190 / 134 us, bf16 2x32x32x32
+// 146 / 132, at 512 KB 144 / 139, at 1 MB 142 / 149; bf16 bottlenecks 20x14x14x64 with 16
+// inner channels 248 / 188, 4x16x16x256 with 64 233 / 214; fp32 bottlenecks 5x14x14x128
+// with 32 249 / 202, but 2x14x14x256 with 64 244 / 273; 64 channels 8x16x16 186 / 187,
+// fp32 8x14x14 238 / 270, and 128 channels 4x16x16 269 / 341.
 constexpr long ONE_STREAM_BYTES = 512l << 10;
 static bool one_stream_step(const petra::Stage& s) {
   const bool neck = s.desc.kind == PETRA_BLOCK_BOTTLENECK;
   return s.blocks.size() == 1 && s.M * s.desc.c_half * static_cast<long>(s.esz) <= ONE_STREAM_BYTES &&
-         (neck ? s.desc.c_mid <= 64 : s.desc.c_half <= 32);
+         (neck ? s.desc.c_mid <= (s.dt == petra::DT_BF16 ? 64 : 32) : s.desc.c_half <= 32);
 }
 
 petra_status petra_stage_step(petra_stage* st, const void* x1, const void* x2, void* y1, void* y2,

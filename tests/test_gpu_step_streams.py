@@ -18,6 +18,10 @@ CASES = {
     "bf16_c32_3x8x8_2": B.with_(n=3, h=8, w=8, blocks=2),
     "fp32_c16_8x8x8": F,
     "bf16_neck_3x14x14": synth.IMAGENET_BOTTLENECK_STAGE.with_(n=3, h=14, w=14, blocks=1),
+    "fp32_neck_c32_3x14x14": synth.IMAGENET_BOTTLENECK_STAGE.with_(n=3, h=14, w=14, blocks=1,
+                                                                   dtype="fp32"),
+    "fp32_neck_c64_3x14x14": synth.IMAGENET_BOTTLENECK_STAGE.with_(n=3, h=14, w=14, blocks=1,
+                                                                   c_mid=64, dtype="fp32"),
 }
 
 
