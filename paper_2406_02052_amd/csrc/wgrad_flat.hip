@@ -50,7 +50,9 @@ struct Cfg {
   // others the input: a wave then holds one side's channel constants and pieces.
   static constexpr int ND = 64 * (NW * WP >= 3 ? NW * WP / 3 : 1), NX = NT - ND;
   static constexpr int D_PT = (P * DG + ND - 1) / ND;
-  // pieces of the input patch per thread: images up to about 60 pixels wide
+  // pieces of the input patch per thread, rounded up: 3x3 plans take images up to 63
+  // pixels wide (fp32: 95 with 16 channels; 61 with 64, by LDS).  One more piece would
+  // be a register more for every width.
   static constexpr int X_PT = ((P + (R == 3 ? 122 : 0)) * XG + NX - 1) / NX;
   static constexpr int MAX_ROWS = X_PT * NX / XG;
   static_assert(TPW * WT == R * R && ND % DG == 0 && NX % XG == 0 && P % (KP * WP) == 0, "tile");

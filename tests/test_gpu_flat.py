@@ -6,7 +6,7 @@ case, are 0.978 apart by themselves in a BN beta the GPU has to 1.7e-5)."""
 import pytest
 
 import synth
-from tests.harness import check, run_step_parity
+from tests.harness import check, gpu_stage, run_step_parity
 
 pytestmark = pytest.mark.gpu
 
@@ -33,7 +33,7 @@ CASES = {
     # 1x1 convs without a kernel of their own
     "bf16_bottleneck_c64_16_3x9x11": NECK.with_(n=3, h=9, w=11, c_half=64, c_mid=16, blocks=1),
     "bf16_bottleneck_c256_64_2x7x7": NECK.with_(n=2, h=7, w=7, c_half=256, c_mid=64, blocks=1),
-    # weight gradients: the widest image whose patch fits and the next one; the
+    # weight gradients: wide images, on flattened pixels and (64 and more) not; the
     # other channel blocks of the 1x1 convs
     "bf16_c64_1x3x63": B.with_(n=1, h=3, w=63, c_half=64, blocks=1),
     "bf16_c64_1x3x64": B.with_(n=1, h=3, w=64, c_half=64, blocks=1),
@@ -54,6 +54,38 @@ CASES = {
     "fp32_bottleneck_c64_16_3x9x11": NECK.with_(n=3, h=9, w=11, c_half=64, c_mid=16, blocks=1,
                                                 dtype="fp32"),
 }
+
+
+# weight gradients: the widest image whose patch a 3x3 plan takes (registers for its rows;
+# fp32, 64 channels: LDS), by type and channel block
+WIDEST = {("bf16", 16): 63, ("bf16", 32): 63, ("bf16", 64): 63,
+          ("fp32", 16): 95, ("fp32", 32): 63, ("fp32", 64): 61}
+
+
+def wgrad_kernels(wl):
+    """Names of the weight-gradient kernels of one backward."""
+    import torch
+    from paper_2406_02052_amd import _lib as L
+
+    st = gpu_stage(wl, synth.stage_params(wl, "random"))
+    y, d, x, dx = ([st.act().normal_() for _ in range(2)] for _ in range(4))
+    L.petra_stage_profile(st.handle, True)
+    st.reconstruct_backward(*y, *d, *x, *dx)
+    torch.cuda.synchronize()
+    return [k[0] for k in L.petra_stage_profile_kernel(st.handle) if k[1] == 2]
+
+
+@pytest.mark.parametrize("dtype,c,wide", [(*k, d) for k in WIDEST for d in (0, 1)])
+def test_widest_weight_gradient(dtype, c, wide):
+    base = F if dtype == "fp32" else B
+    wl = base.with_(n=1, h=3, w=WIDEST[dtype, c] + wide, c_half=c, blocks=1)
+    print(f"case {wl}", flush=True)
+    names = wgrad_kernels(wl)
+    print(names, flush=True)
+    assert all(("wgrad_flat" in k) == (wide == 0) for k in names) and names
+    for mode in ("isoF", "isoG") if dtype == "bf16" else ("full",):
+        got, want, exact = run_step_parity(wl, bn_affine="random", mode=mode, anchor=False)
+        print(check(wl, mode, got, want, exact), flush=True)
 
 
 @pytest.mark.parametrize("name,mode", [(n, m) for n, wl in CASES.items()
