@@ -327,9 +327,8 @@ void bn_stats_finalize(const float* partials, int tiles, int c, long m, const fl
 }
 
 void bn_bwd_finalize(const float* partials, int tiles, int c, long m, const float* gamma,
-                     const float* mean, const float* rstd, float inv_k, float* dgamma,
-                     float* dbeta, float* ca, float* cb, float* cc, hipStream_t st) {
-  (void)mean;   // the partials of d xhat are centred
+                     const float* rstd, float inv_k, float* dgamma, float* dbeta, float* ca,
+                     float* cb, float* cc, hipStream_t st) {
   const double inv_m = m > 0 ? 1.0 / static_cast<double>(m) : 0.0;
   PETRA_FINALIZE(bn_bwd_finalize_kernel, partials, tiles, c, inv_m, gamma, rstd, inv_k, dgamma,
                  dbeta, ca, cb, cc);

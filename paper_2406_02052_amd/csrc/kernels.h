@@ -164,8 +164,8 @@ void bn_stats_finalize(const float* partials, int tiles, int c, long m, const fl
 // inv_k*dgamma, inv_k*dbeta to the gradient accumulator and writes the
 // coefficients of dh = ca*d + cb*(h - mean) + cc.
 void bn_bwd_finalize(const float* partials, int tiles, int c, long m, const float* gamma,
-                     const float* mean, const float* rstd, float inv_k, float* dgamma,
-                     float* dbeta, float* ca, float* cb, float* cc, hipStream_t st);
+                     const float* rstd, float inv_k, float* dgamma, float* dbeta, float* ca,
+                     float* cb, float* cc, hipStream_t st);
 
 // Row-chunk count used by the reducing elementwise kernel for m rows.
 int ew_tiles(long m, int c);

@@ -497,7 +497,7 @@ void Net::front_backward(NetStage& s, const void* in1, const void* in2, const vo
   const int relu = s.first ? 1 : 0;
   split_bwd_partials(dt, d1, d2, ws + s.o_bh, scale, shift, mean, rstd, relu,
                      at<float>(s.o_bpart), s.M, s.C, q);
-  bn_bwd_finalize(at<float>(s.o_bpart), split_tiles(s.M, s.C), s.C, s.M, fv.gamma, mean, rstd,
+  bn_bwd_finalize(at<float>(s.o_bpart), split_tiles(s.M, s.C), s.C, s.M, fv.gamma, rstd,
                   inv_k, grad + s.off_front_g, grad + s.off_front_b, ca, cb, cc, q);
   split_bwd_apply(dt, d1, d2, ws + s.o_bh, scale, shift, ca, cb, cc, mean, relu, ws + s.o_dh,
                   s.M, s.C, q);

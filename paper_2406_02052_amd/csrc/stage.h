@@ -37,8 +37,9 @@ struct Block {
 
 // Device scratch of one residual function's pass, carved from the workspace.
 // The forward uses one set; the backward alternates two sets between
-// consecutive residual functions, so the recompute of the next function can run
-// while the gradient chain of the current one still reads its own set.
+// consecutive residual functions (or has one for each, see keep_sets), so the
+// recompute of the next function can run while the gradient chain of the current
+// one still reads its own set.
 struct Scratch {
   void* h[3] = {nullptr, nullptr, nullptr};  // pre-BN conv outputs of the function
   void* d1[2] = {nullptr, nullptr};          // masked gradients dz of inner layers (backward)
@@ -190,10 +191,8 @@ class Stage {
 
   GraphCache graphs;
   bool use_graphs = false;
-  // 1: one stream; 2: + weight gradients; 3: + recompute ahead.  Set in the
-  // constructor: one stream for basic blocks (each cross-stream event costs more
-  // host time than the overlap gains there), three for bottleneck blocks (their
-  // HBM-bound 1x1 convs overlap well).
+  // 1: one stream; 2: + weight gradients; 3: + recompute ahead.  One by default: each
+  // cross-stream event costs more host time than the overlap gains.
   int bwd_streams = 1;
 
  private:

@@ -15,11 +15,13 @@
 //               applies the ReLU mask of the layer below and emits that layer's
 //               BN-backward partials, or, for the first layer, adds rg
 //               (dout = rg + dPhi/du^T d) and emits the BN_L-backward partials of
-//               the next function visited; the weight gradient of each conv runs
-//               on a side stream from the same on-the-fly dh (split rows,
-//               fixed-order reduce into the accumulator, scaled 1/k).
-// The recompute of the next function runs on its own stream while the gradient
-// chain of the current one proceeds; two scratch sets alternate between them.
+//               the next function visited; the weight gradient of each conv
+//               forms the same dh on the fly and runs with the others of the
+//               function or of the whole backward (split rows, fixed-order
+//               reduce into the accumulator, scaled 1/k).
+// With more than one stream the weight gradients go to a side stream and the
+// recompute of the next function to its own, while the gradient chain of the
+// current one proceeds; two scratch sets alternate, or each function has its own.
 #include <algorithm>
 #include <cstring>
 
@@ -471,7 +473,7 @@ void Stage::fn_grad(const BwdFn& f, Scratch& s, const BwdFn* next, Scratch* sn, 
     const ConvLayer& cv = convs[fn.conv[L]];
     const BnLayer& bn = bns[cv.bn];
     prof.begin(st);
-    bn_bwd_finalize(s.part, s.gtiles, cv.cout, M, v_th + bn.g_off, s.vec(L, V_MEAN, cmax),
+    bn_bwd_finalize(s.part, s.gtiles, cv.cout, M, v_th + bn.g_off,
                     s.vec(L, V_RSTD, cmax), inv_k, grad + bn.g_off, grad + bn.b_off,
                     s.vec(L, V_CA, cmax), s.vec(L, V_CB, cmax), s.vec(L, V_CC, cmax), st);
     prof.end(K_BN_BWD_FINALIZE, st, 0.0, 8.0 * s.gtiles * cv.cout);
@@ -514,7 +516,7 @@ void Stage::fn_grad(const BwdFn& f, Scratch& s, const BwdFn* next, Scratch* sn, 
       conv(a, EP_MASK, st);
       prof.end(K_CONV_DGRAD, st, 2.0 * M * cv.cin * a.k_tot, dbytes);
       prof.begin(st);
-      bn_bwd_finalize(s.part, tiles_conv, lo.cout, M, v_th + bl.g_off, s.vec(l - 1, V_MEAN, cmax),
+      bn_bwd_finalize(s.part, tiles_conv, lo.cout, M, v_th + bl.g_off,
                       s.vec(l - 1, V_RSTD, cmax), inv_k, grad + bl.g_off, grad + bl.b_off,
                       s.vec(l - 1, V_CA, cmax), s.vec(l - 1, V_CB, cmax),
                       s.vec(l - 1, V_CC, cmax), st);
